@@ -110,8 +110,7 @@ __device__ __forceinline__ void launder_key(uint32_t& a, uint32_t& c) {
 // instead of three.
 struct StreamAt {
     uint32_t k0, k1;    // key
-    uint32_t ghi;       // hi16(g)
-    uint32_t u0;        // hi(M1 n0) ^ k0: round-0 word 0 without the block's word 1
+    uint32_t u0;        // hi(M1 n0) ^ k0 ^ hi16(g): round-0 word 0 without the block's tag and number
     uint32_t c3k;       // round-0 output word 3 ^ round-1 key 1
     uint32_t c1k;       // round-1 output word 1 ^ round-2 key 0
     uint32_t h2k;       // hi(M0 c0) of round 2 ^ round-2 key 1
@@ -120,7 +119,7 @@ struct StreamAt {
     __device__ __forceinline__ Words4 block(uint32_t tag, uint32_t b) const {
         uint32_t a = k0, c = k1;
         launder_key(a, c);
-        const uint32_t x0 = u0 ^ (ghi | (tag << 16) | (b << 24));              // round 0, word 0
+        const uint32_t x0 = u0 ^ ((tag << 16) | (b << 24));                      // round 0, word 0
         const uint64_t p0 = (uint64_t)PHILOX_M0 * x0;                          // round 1
         const uint32_t y2 = (uint32_t)(p0 >> 32) ^ c3k;
         const uint32_t y3 = (uint32_t)p0;
@@ -157,8 +156,7 @@ struct Stream {
         const uint64_t Q2 = (uint64_t)PHILOX_M0 * c0b;                        // round 2
         return StreamAt{k0,
                         k1,
-                        (uint32_t)(g >> 32) & 0xFFFFu,
-                        (uint32_t)(P1 >> 32) ^ a,
+                        (uint32_t)(P1 >> 32) ^ a ^ ((uint32_t)(g >> 32) & 0xFFFFu),
                         (uint32_t)P0 ^ (c + PHILOX_W1),
                         (uint32_t)Q1 ^ (a + 2u * PHILOX_W0),
                         (uint32_t)(Q2 >> 32) ^ (c + 2u * PHILOX_W1),
@@ -198,6 +196,49 @@ __device__ __forceinline__ uint64_t mad_u64_u32(uint32_t a, uint32_t b, uint64_t
     return d;
 }
 
+// a * b, b uniform, in one v_mad_u64_u32 (a power of two b would otherwise
+// become a shift for each word).
+__device__ __forceinline__ uint64_t mul_wide_s(uint32_t a, uint32_t b) {
+    uint64_t d, carry;
+    asm("v_mad_u64_u32 %0, %1, %2, %3, 0" : "=v"(d), "=s"(carry) : "v"(a), "s"(b));
+    return d;
+}
+
+// a * b + C with the low 24 bits of a and b, C an inline constant (-16..64).
+template <int C>
+__device__ __forceinline__ uint32_t mad24(uint32_t a, uint32_t b) {
+    uint32_t d;
+    asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "n"(C));
+    return d;
+}
+
+// a + b with its carry, as 64 bits.
+__device__ __forceinline__ uint64_t add_wide(uint32_t a, uint32_t b) {
+    uint32_t lo, hi;
+    asm("v_add_co_u32 %0, vcc, %2, %3\n\tv_addc_co_u32 %1, vcc, 0, 0, vcc" : "=&v"(lo), "=v"(hi) : "v"(a), "v"(b) : "vcc");
+    return join64(lo, hi);
+}
+
+// Low or high half of `pair` times the low half of r, plus c, in 32 bits (one
+// v_mad_u32_u16; its operand select reads a half without unpacking it).
+template <bool HIGH>
+__device__ __forceinline__ uint32_t mad_half(uint32_t pair, uint32_t r, uint32_t c) {
+    uint32_t d;
+    if constexpr (HIGH)
+        asm("v_mad_u32_u16 %0, %1, %2, %3 op_sel:[1,0,0,0]" : "=v"(d) : "v"(pair), "v"(r), "v"(c));
+    else
+        asm("v_mad_u32_u16 %0, %1, %2, %3" : "=v"(d) : "v"(pair), "v"(r), "v"(c));
+    return d;
+}
+
+// p^-1 mod 2^32 for odd p (Newton: each step doubles the valid low bits, the
+// start p holds 3 of them).
+__host__ __device__ constexpr uint32_t inverse32(uint32_t p) {
+    uint32_t v = p;
+    for (int i = 0; i < 4; ++i) v *= 2u - p * v;
+    return v;
+}
+
 // p < 2^12.  a, b < p, so a*b < 2^24 is exact in one v_mul_u32_u24 and in
 // fp32.  The fp32 quotient is within one of floor(x / p); two corrections.
 struct FieldSmall {
@@ -206,13 +247,17 @@ struct FieldSmall {
     static constexpr bool kDefault = false;   // any prime below 2^12
     uint32_t p;
     float pinv;
+    uint32_t p_inv32;                         // p^-1 mod 2^32
+    __device__ __forceinline__ uint32_t pinv32() const { return p_inv32; }
     __device__ __forceinline__ uint32_t reduce24(uint32_t x) const {   // x < 2^24
         const uint32_t q = (uint32_t)((float)x * pinv);
         uint32_t r = x - __umul24(q, p);   // in (-p, 2p), mod 2^32
         r = min(r, r + p);                 // negative: the wrapped r + p is the small one
         return min(r, r - p);              // >= p: r - p; else r - p wraps and r stays
     }
-    __device__ __forceinline__ FieldSmall vgpr() const { return FieldSmall{in_vgpr(p), in_vgpr(pinv)}; }
+    __device__ __forceinline__ FieldSmall vgpr() const {
+        return FieldSmall{in_vgpr(p), in_vgpr(pinv), in_vgpr(p_inv32)};
+    }
     __device__ __forceinline__ uint32_t mul(uint32_t a, uint32_t b) const { return reduce24(__umul24(a, b)); }
     // a, b, c < p: a*b + c <= p^2 - p < 2^24 as well.
     __device__ __forceinline__ uint32_t mul_add(uint32_t a, uint32_t b, uint32_t c) const {
@@ -232,7 +277,7 @@ struct FieldMersenne {
     // issue at about twice the rate with literal or VGPR operands as with an
     // SGPR operand.
     static constexpr uint32_t p = (1u << K) - 1;
-    static constexpr bool kLazy = true;       // the *_lazy forms: a value below 2p, 4p < 2^32
+    static constexpr __device__ uint32_t pinv32() { return inverse32(p); }
     __device__ __forceinline__ FieldMersenne vgpr() const { return *this; }
     __device__ __forceinline__ uint32_t mul(uint32_t a, uint32_t b) const {
         const uint64_t x = (uint64_t)a * b;
@@ -240,14 +285,10 @@ struct FieldMersenne {
         return min(s, s - p);             // s < p: s - p wraps above s
     }
     // a, b, c < p: x = a*b + c <= p^2 - p, so x >> K <= p - 2 and the fold is
-    // still below 2p; the addend rides in the multiply.  The lazy form stops
-    // before the conditional subtraction.
-    __device__ __forceinline__ uint32_t mul_add_lazy(uint32_t a, uint32_t b, uint32_t c) const {
-        const uint64_t x = mad_u64_u32(a, b, c);
-        return ((uint32_t)x & p) + (uint32_t)(x >> K);
-    }
+    // still below 2p; the addend rides in the multiply.
     __device__ __forceinline__ uint32_t mul_add(uint32_t a, uint32_t b, uint32_t c) const {
-        const uint32_t s = mul_add_lazy(a, b, c);
+        const uint64_t x = mad_u64_u32(a, b, c);
+        const uint32_t s = ((uint32_t)x & p) + (uint32_t)(x >> K);
         return min(s, s - p);
     }
     // The same with b and c given shifted left by SH = 32 - K (b_sh = b 2^SH,
@@ -255,14 +296,10 @@ struct FieldMersenne {
     // splits at bit 32 into x >> K (high word) and (x mod 2^K) 2^SH (low
     // word), so the fold takes one shift instead of a funnel shift.
     template <int SH>
-    __device__ __forceinline__ uint32_t mul_add_sh_lazy(uint32_t a, uint32_t b_sh, uint32_t c_sh) const {
+    __device__ __forceinline__ uint32_t mul_add_sh(uint32_t a, uint32_t b_sh, uint32_t c_sh) const {
         static_assert(SH == 32 - K, "operands shifted to the top of the word");
         const uint64_t x = mad_u64_u32(a, b_sh, c_sh);
-        return ((uint32_t)x >> SH) + (uint32_t)(x >> 32);
-    }
-    template <int SH>
-    __device__ __forceinline__ uint32_t mul_add_sh(uint32_t a, uint32_t b_sh, uint32_t c_sh) const {
-        const uint32_t s = mul_add_sh_lazy<SH>(a, b_sh, c_sh);
+        const uint32_t s = ((uint32_t)x >> SH) + (uint32_t)(x >> 32);
         return min(s, s - p);
     }
 };
@@ -281,12 +318,12 @@ struct FieldPM {
     static constexpr bool kWrap = K == 32;   // p > 2^31: 32-bit sums can wrap
     static constexpr bool kDefault = true;   // the largest prime below 2^K
     static constexpr uint32_t p = (uint32_t)((1ull << K) - CC);
+    static constexpr __device__ uint32_t pinv32() { return inverse32(p); }
     static constexpr uint32_t LOW = (uint32_t)((1ull << K) - 1);
-    static constexpr bool kLazy = K <= 30;   // the *_lazy forms: a value below 2p, 4p < 2^32
     __device__ __forceinline__ FieldPM vgpr() const { return *this; }
     __device__ __forceinline__ uint32_t mul(uint32_t a, uint32_t b) const { return mul_add(a, b, 0); }
     // Both folds, without the final conditional subtraction: below 2p (K < 32).
-    __device__ __forceinline__ uint32_t mul_add_lazy(uint32_t a, uint32_t b, uint32_t d) const {
+    __device__ __forceinline__ uint32_t folded(uint32_t a, uint32_t b, uint32_t d) const {
         static_assert(K < 32, "the 32-bit fold ends differently");
         if constexpr (K <= 12) {
             // x < p^2 < 2^24: every step in 32 bits with 24-bit multiply-adds
@@ -312,7 +349,7 @@ struct FieldPM {
     }
     __device__ __forceinline__ uint32_t mul_add(uint32_t a, uint32_t b, uint32_t d) const {
         if constexpr (K < 32) {
-            const uint32_t S = mul_add_lazy(a, b, d);
+            const uint32_t S = folded(a, b, d);
             return min(S, S - p);
         }
         // K = 32: 64-bit folds, and S = L2 + c H2 < 2^32 + c^2 may exceed 32
@@ -327,16 +364,12 @@ struct FieldPM {
     // mul_add with b and d given shifted left by SH = 32 - K (12 < K <= 24):
     // x 2^SH splits at bit 32 into H = x >> K and L 2^SH, L = x mod 2^K.
     template <int SH>
-    __device__ __forceinline__ uint32_t mul_add_sh_lazy(uint32_t a, uint32_t b_sh, uint32_t d_sh) const {
+    __device__ __forceinline__ uint32_t mul_add_sh(uint32_t a, uint32_t b_sh, uint32_t d_sh) const {
         static_assert(SH == 32 - K && K > 12 && K <= 24, "operands shifted to the top of the word");
         const uint64_t x = mad_u64_u32(a, b_sh, d_sh);
         const uint32_t H = (uint32_t)(x >> 32), L = (uint32_t)x >> SH;
         const uint32_t t = __umul24(H, CC) + L;                    // < 2^(K + 6) <= 2^30
-        return (t & LOW) + __umul24(t >> K, CC);                   // < 2^K + c^2 < 2p
-    }
-    template <int SH>
-    __device__ __forceinline__ uint32_t mul_add_sh(uint32_t a, uint32_t b_sh, uint32_t d_sh) const {
-        const uint32_t S = mul_add_sh_lazy<SH>(a, b_sh, d_sh);
+        const uint32_t S = (t & LOW) + __umul24(t >> K, CC);       // < 2^K + c^2 < 2p
         return min(S, S - p);
     }
 };
@@ -353,6 +386,7 @@ struct FieldPM33 {
     static constexpr bool kDefault = true;    // the largest prime below 2^33
     static constexpr uint64_t p = (1ull << 33) - 9;
     static constexpr uint64_t LOW33 = (1ull << 33) - 1;
+    static constexpr __device__ uint32_t pinv32() { return inverse32((uint32_t)p); }
     __device__ __forceinline__ FieldPM33 vgpr() const { return *this; }
     __device__ __forceinline__ uint64_t mul(uint64_t a, uint64_t b) const { return mul_add(a, b, 0); }
     __device__ __forceinline__ uint64_t mul_add(uint64_t a, uint64_t b, uint64_t d) const {
@@ -383,7 +417,9 @@ struct Field24 {
     static constexpr bool kDefault = false;   // any prime of its range
     uint32_t p;
     double pd, pinv;
-    __device__ __forceinline__ Field24 vgpr() const { return Field24{in_vgpr(p), pd, pinv}; }
+    uint32_t p_inv32;                         // p^-1 mod 2^32
+    __device__ __forceinline__ uint32_t pinv32() const { return p_inv32; }
+    __device__ __forceinline__ Field24 vgpr() const { return Field24{in_vgpr(p), pd, pinv, in_vgpr(p_inv32)}; }
     __device__ __forceinline__ uint32_t mul(uint32_t a, uint32_t b) const {
         return reduce((double)a * (double)b);
     }
@@ -408,7 +444,9 @@ struct Field32 {
     static constexpr bool kDefault = false;   // any prime of its range
     uint32_t p;
     uint64_t mu;
-    __device__ __forceinline__ Field32 vgpr() const { return Field32{in_vgpr(p), mu}; }
+    uint32_t p_inv32;                         // p^-1 mod 2^32
+    __device__ __forceinline__ uint32_t pinv32() const { return p_inv32; }
+    __device__ __forceinline__ Field32 vgpr() const { return Field32{in_vgpr(p), mu, in_vgpr(p_inv32)}; }
     __device__ __forceinline__ uint32_t mul(uint32_t a, uint32_t b) const {
         return reduce((uint64_t)a * b);
     }
@@ -462,17 +500,6 @@ __device__ __forceinline__ typename F::T addmod(typename F::T a, typename F::T b
     return min(s, (FT)(s - f.p));         // s < p: s - p wraps above s
 }
 
-// a, b < p: (a - b) mod p.  Without wrap (2p <= 2^bits) the wrapped
-// difference plus p is the answer exactly when a < b, and it is then the
-// smaller of the two: one subtraction, one addition and one min.
-template <typename F>
-__device__ __forceinline__ typename F::T submod(typename F::T a, typename F::T b, const F& f) {
-    using FT = typename F::T;
-    const FT d = a - b;
-    if constexpr (F::kWrap) return a < b ? d + f.p : d;
-    return min(d, (FT)(d + f.p));
-}
-
 // Orders one wave's LDS accesses across its lanes: the lanes of a wave run
 // in lockstep and the LDS serves a wave's instructions in order, so only the
 // compiler must be kept from moving accesses across this point.
@@ -484,7 +511,10 @@ __device__ __forceinline__ void wave_sync() {
 
 // r_s in Z_p^* and z_s in Z_p by multiply-shift of uniform 32-bit words
 // (p < 2^32): r = 1 + floor(R (p - 1) / 2^32), z = floor(Z p / 2^32).
-__device__ __forceinline__ uint32_t draw_r(uint32_t R, uint32_t p) { return 1u + __umulhi(R, p - 1u); }
+// The 1 rides in the multiply.
+__device__ __forceinline__ uint32_t draw_r(uint32_t R, uint32_t p) {
+    return (uint32_t)(mad_u64_u32(R, p - 1u, 1ull << 32) >> 32);
+}
 __device__ __forceinline__ uint32_t draw_z(uint32_t Z, uint32_t p) { return __umulhi(Z, p); }
 
 }  // namespace bc

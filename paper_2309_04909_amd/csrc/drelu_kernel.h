@@ -61,32 +61,20 @@ __device__ __forceinline__ FT window_low(T a, uint32_t pos) {
         return (FT)(a >> pos);
 }
 
-// Bits [pos, pos + l_x] of a share already shifted down by k_lo (pos <= l_x).
-template <typename T, int N, typename FT>
-__device__ __forceinline__ FT window(T a, uint32_t pos) {
-    constexpr FT WIN1 = (FT)((2ull << (N - 1)) - 1);     // l_x + 1 bits
-    return window_low<T, N, FT>(a, pos) & WIN1;
-}
-
 // a * b + c in Z_p with b and c given shifted left by SH bits (SH = 0: the
-// plain values; see MaskDraws).  LAZY: a value below 2p congruent to it
-// (the field's form without the final conditional subtraction).
-template <int SH, typename F, bool LAZY = false>
+// plain values; see MaskDraws).
+template <int SH, typename F>
 __device__ __forceinline__ typename F::T field_mul_add(const F& f, typename F::T a, typename F::T b, typename F::T c) {
-    if constexpr (LAZY) {
-        if constexpr (SH == 0)
-            return f.mul_add_lazy(a, b, c);
-        else
-            return f.template mul_add_sh_lazy<SH>(a, b, c);
-    } else if constexpr (SH == 0) {
+    if constexpr (SH == 0)
         return f.mul_add(a, b, c);
-    } else {
+    else if constexpr (SH < 8)
+        return f.mul_add(a, b >> SH, c >> SH);        // N > 24: the fields fold from plain values
+    else
         return f.template mul_add_sh<SH>(a, b, c);
-    }
 }
 
-// P1's reshare addend p - z, kept shifted by SH like z, from a z whose low
-// SH bits may carry stray bits (stream_draws): they are masked first.
+// P1's reshare addend p - z, kept shifted by SH like z, from a z <= p whose
+// low SH bits may carry stray bits (stream_draws): they are masked first.
 template <int SH, typename F>
 __device__ __forceinline__ typename F::T reshare_neg(const F& f, typename F::T z) {
     using FT = typename F::T;
@@ -94,120 +82,223 @@ __device__ __forceinline__ typename F::T reshare_neg(const F& f, typename F::T z
     return (FT)((f.p << SH) - (FT)(z & KEEP));
 }
 
-// Whether field F offers the lazy forms (a value below 2p with 4p < 2^32).
-template <typename F, typename = void>
-struct HasLazy : std::false_type {};
-template <typename F>
-struct HasLazy<F, std::void_t<decltype(F::kLazy)>> : std::integral_constant<bool, F::kLazy> {};
-
 // v_min3_u32 written out: the compiler would otherwise re-associate P2's
 // running minimum into a tree over all slots, which defers every slot's
-// fold to the end and keeps all the products live at once.
+// end and keeps all of them live at once.
 __device__ __forceinline__ uint32_t min3_in_order(uint32_t a, uint32_t b, uint32_t c) {
     uint32_t d;
     asm("v_min3_u32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
     return d;
 }
 
-// P2's running minimum over the slots of w0 + w1 mod p (a slot is zero
-// exactly when its reconstruction is 0): without wrap, min(least, s, s - p)
-// is one three-operand minimum, taken slot after slot.
-template <typename F>
-__device__ __forceinline__ typename F::T p2_least(typename F::T least, typename F::T w0, typename F::T w1, const F& f) {
-    using FT = typename F::T;
-    if constexpr (F::kWrap) {
-        const FT w = addmod(w0, w1, f);
-        FT m = w < least ? w : least;
-        asm("" : "+v"(m));                          // slot by slot, as min3_in_order does
-        return m;
-    } else if constexpr (sizeof(FT) == 4) {
-        const FT s = w0 + w1;
-        return min3_in_order(least, s, s - f.p);
-    } else {
-        const FT s = w0 + w1;
-        FT m = min(least, min(s, (FT)(s - f.p)));
-        asm("" : "+v"(m));                          // slot by slot, as min3_in_order does
-        return m;
-    }
-}
-
-// P2's running minimum from two lazy messages w0, w1 < 2p (4p < 2^32): their
-// sum t < 4p, u = t mod 2p by one conditional subtraction, then u and u - p
-// into the minimum as in p2_least; u is 0 or p exactly when t is 0 mod p.
-template <typename F>
-__device__ __forceinline__ uint32_t p2_least_lazy(uint32_t least, uint32_t w0, uint32_t w1, const F& f) {
-    const uint32_t t = w0 + w1;
-    const uint32_t u = min(t, t - 2 * f.p);
-    return min3_in_order(least, u, u - f.p);
-}
-
-// Windows through P2's reconstruction (Alg. 7) for one slot: the window
-// position `pos` (sigma of the slot), the slot's mask r and reshare z (both
-// shifted left by SH bits, see MaskDraws); returns both parties' messages
-// and folds P2's reconstruction w0 + w1 mod p into its running minimum
-// `least` (some slot is zero exactly when the minimum ends at 0).
-// a0 and nb1 are P0's share and P1's negated share, both shifted down by k_lo.
-// Every select is written as masks and adds so that it stays on the
-// full-rate VOP2 forms (no compare / cndmask pairs).  With LAZY (callers
-// that only test the slot, not capture its messages) and a field that has
-// the lazy forms, w0 and w1 are left below 2p, one congruent value each, and
-// P2 reduces their sum once.
-// `next_w` is the width of u_{i+1}: l_x, or 0 when pos = l_x (u_{l_x+1} :=
-// 0); the overload without it derives it from pos.
-template <typename T, int N, typename F, int SH = 0, bool LAZY = false>
-__device__ __forceinline__ void slot_messages(T a0, T nb1, uint32_t pos, uint32_t next_w, typename F::T r,
-                                              typename F::T z, const F& f, typename F::T& w0, typename F::T& w1,
-                                              typename F::T& least) {
-    using FT = typename F::T;
+// The adjacent sums of one window position (sigma of a slot), before the
+// modulo switch (Alg. 7, Alg. 6):
+//   P0   v_0 = (u_i + u_{i+1} - 2) mod 2^l_x; its switched value, v mod p of
+//        v = u_i + u_{i+1} - 1 with 0 standing as 2^l_x, is s_0 = v_0 + 1
+//   P1   v_1 = (cut_i + cut_{i+1} - 1) mod 2^l_x; its switched value
+//        -(cut_i + cut_{i+1}) mod 2^l_x + p - 2^l_x is p - (v_1 + 1)
+// a is P0's share or P1's negated share, flipped and shifted down by k_lo.
+// With W = a >> pos, u_i + u_{i+1} = W + floor(W / 2) = floor(3 W / 2) in
+// bits [0, l_x), and for pos = l_x (u_{l_x+1} := 0) floor(2 W / 2): so
+// v = (times W - 2 minus) >> 1 mod 2^l_x with times = 3, or 2 for pos = l_x, which
+// the shuffle keeps beside the position.  Bits of W above the window only
+// reach bits above the sum.  Three operations a party: the shift, one
+// multiply-add, one bit-field extract.
+template <typename T, int N, int MINUS>
+__device__ __forceinline__ uint32_t window_sum(T a, uint32_t pos, uint32_t times) {
     constexpr int LX = N - 1;
-    constexpr FT TWO_LX = (FT)1 << LX;                   // 2^l_x mod p = 2^l_x
-    constexpr FT WIN = TWO_LX - 1;                       // Z_{2^l_x}
-    // W: bits [k_lo + pos, k_lo + pos + l_x] in bits [0, l_x]; with 32-bit
-    // field elements the bits above are left in place, since u_{i+1} reads
-    // bits [1, 1 + next_w) only and everything after is reduced mod 2^l_x
-    FT W0, W1, u0n, u1n;                                 // u_{i+1}, and u_{l_x+1} := 0
-    if constexpr (sizeof(FT) == 4) {
-        W0 = window_low<T, N, FT>(a0, pos);
-        W1 = window_low<T, N, FT>(nb1, pos);
-        u0n = __builtin_amdgcn_ubfe(W0, 1, next_w);
-        u1n = __builtin_amdgcn_ubfe(W1, 1, next_w);
-    } else {
-        W0 = window<T, N, FT>(a0, pos);
-        W1 = window<T, N, FT>(nb1, pos);
-        const FT more = (FT)0 - (FT)(next_w != 0);
-        u0n = (W0 >> 1) & more;
-        u1n = (W1 >> 1) & more;
-    }
-    // adjacent sum and modulo switch (Alg. 6) for P0: v0 = u_i + u_{i+1} - 1 in Z_{2^l_x},
-    // s0 = v0, or 2^l_x when v0 = 0, which is ((v0 - 1) mod 2^l_x) + 1.
-    const FT s0 = ((W0 + u0n - 2) & WIN) + 1;
-    // P1: v1 = -(cut_i + cut_{i+1}) in Z_{2^l_x} and s1 = v1 + p - 2^l_x,
-    // which is (p - 1) - ((cut_i + cut_{i+1} - 1) mod 2^l_x)
-    const FT s1 = (f.p - 1) - ((W1 + u1n - 1) & WIN);
-    if constexpr (LAZY && HasLazy<F>::value) {
-        w0 = field_mul_add<SH, F, true>(f, s0, r, z);
-        w1 = field_mul_add<SH, F, true>(f, s1, r, reshare_neg<SH>(f, z));
-        least = p2_least_lazy(least, w0, w1, f);
-    } else {
-        w0 = field_mul_add<SH>(f, s0, r, z);                           // mask, reshare
-        w1 = field_mul_add<SH>(f, s1, r, reshare_neg<SH>(f, z));       // P1: s1 r - z
-        least = p2_least(least, w0, w1, f);                            // P2 reconstructs and tests
+    if constexpr (N <= 24)                                   // W's low 24 bits hold the window and u_{i+1}
+        return __builtin_amdgcn_ubfe(mad24<-2 * MINUS>(window_low<T, N, uint32_t>(a, pos), times), 1, LX);
+    else if constexpr (N <= 32)
+        return __builtin_amdgcn_ubfe(
+            (uint32_t)mad_u64_u32(window_low<T, N, uint32_t>(a, pos), times, 0ull - 2 * MINUS), 1, LX);
+    else {                                                   // 32-bit windows of a 64-bit share
+        const uint64_t W = a >> pos;
+        return (uint32_t)W + ((uint32_t)(W >> 1) & (2u - times)) - MINUS;
     }
 }
-
-template <typename T, int N, typename F, int SH = 0, bool LAZY = false>
-__device__ __forceinline__ void slot_messages(T a0, T nb1, uint32_t pos, typename F::T r, typename F::T z, const F& f,
-                                              typename F::T& w0, typename F::T& w1, typename F::T& least) {
-    const uint32_t more_mask = (uint32_t)((int32_t)(pos - (uint32_t)(N - 1)) >> 31);   // all ones unless pos = l_x
-    slot_messages<T, N, F, SH, LAZY>(a0, nb1, pos, (uint32_t)(N - 1) & more_mask, r, z, f, w0, w1, least);
+template <typename T, int N>
+__device__ __forceinline__ void window_sums(T a0, T nb1, uint32_t pos, uint32_t times, uint32_t& v0, uint32_t& v1) {
+    v0 = window_sum<T, N, 2>(a0, pos, times);
+    v1 = window_sum<T, N, 1>(nb1, pos, times);
+}
+template <typename T, int N>
+__device__ __forceinline__ void window_sums(T a0, T nb1, uint32_t pos, uint32_t& v0, uint32_t& v1) {
+    window_sums<T, N>(a0, nb1, pos, 3u - (pos + 1) / N, v0, v1);    // 2 at pos = l_x = N - 1
 }
 
-// (-1)^t v mod 2^l for v < 2^l (Alg. 7's flip).  A select: the select-free
-// form (v ^ -t) + t compiled to 36 more instructions and 74 VGPRs in the
-// N = 19 DReLU kernel.
+// Both parties' round-1 messages of one slot in [0, p), from its sums and its
+// plain mask r and reshare z: w0 = s_0 r + z, w1 = s_1 r - z.
+template <typename F>
+__device__ __forceinline__ void slot_messages(uint32_t v0, uint32_t v1, typename F::T r, typename F::T z, const F& f,
+                                              typename F::T& w0, typename F::T& w1) {
+    using FT = typename F::T;
+    w0 = f.mul_add((FT)v0 + 1, r, z);
+    w1 = f.mul_add((FT)(f.p - 1) - (FT)v1, r, (FT)(f.p - z));
+}
+
+// P2's test of one slot where nothing captures the messages.  P1 keeps its
+// message negated, as it keeps its negated share: s_1 r - z is
+// -((v_1 + 1) r + z) mod p.  So both parties form m = v r + c with
+// c = r + z, unreduced (a value congruent to the message, or to its
+// negation), and P2 reconstructs by subtraction: the slot is zero exactly
+// when p divides D = m0 - m1.  mark() is at most LIMIT for these slots and
+// above it for all others; P2 keeps the minimum.  No division or reduction
+// is needed for that: with p' = p^-1 mod 2^32, k = D p' mod 2^32 (as a signed
+// number) is the only candidate for the quotient, so
+//  * p < 2^16 (N <= 16): |D| < 2^31 and a quotient has |k| <= K = 2^l_x - 1.  No
+//    other D in that range has k in [-K, K] (|k| p < 2^31), so the test is
+//    D p' + K mod 2^32 <= 2 K, one multiply-add.
+//  * p < 2^31: r and z are kept shifted left by SH, and D with them;
+//    |D| < 2^62 and a quotient is below 2^31 in magnitude (l_x + SH <= 31).
+//    D - k p has a zero low word, so p divides D exactly when its high word
+//    is zero.
+//  * p in (2^31, 2^32): the same, as (D + (2^32 - p) k) = k 2^32.
+//  * p = 2^33 - 9: 2^33 = 9 mod p, so twice a message v r + c,
+//    r = r_1 2^32 + r_0, is 9 (hi(v r_0) + v r_1) + 2 lo(v r_0) + 2 c, below
+//    2^38; a quotient of the two's difference U is at most 32 in magnitude, so
+//    k is taken from its low 8 bits and U + 9 k = k 2^33 decides.
+//  * any other prime above 2^32: the messages in [0, p), compared.
+// The products are opaque to the compiler (asm), which would otherwise
+// subtract the shares before masking them.
+// These kernels are bound by VALU issue, about 4.1 cycles an instruction
+// whatever its kind, so the instruction count decides.  With the reduced
+// messages and their compares replaced by this test, the packed windows, the
+// grouped shuffle digits and window_sum (886 -> 725 instructions an element
+// at N = 19, 647 -> 463 for the N = 8 ReLU): DReLU at N = 19 and 2^24
+// elements 0.360 -> 0.298 ms, ReLU at N = 8 0.255 -> 0.209 ms; DReLU at
+// N = 32 and 2^23 0.378 -> 0.277 ms, at N = 33 and 2^22 0.422 -> 0.231 ms.
+template <int N, typename F, int SH>
+struct SlotTest {
+    using FT = typename F::T;
+    static constexpr bool SMALL = N <= 16;
+    static constexpr uint32_t K = SMALL ? (1u << (N - 1)) - 1 : 0;
+    static constexpr uint32_t LIMIT = 2 * K;
+
+    static __device__ __forceinline__ uint32_t mark_small(uint32_t m0, uint32_t m1, const F& f) {
+        return (uint32_t)mad_u64_u32(m0 - m1, f.pinv32(), K);
+    }
+    // Both sums in one word, v_0 in the low half and v_1 in the high half.
+    static __device__ __forceinline__ uint32_t mark_pair(uint32_t pair, uint32_t r, uint32_t z, const F& f) {
+        const uint32_t c = r + z;
+        return mark_small(mad_half<false>(pair, r, c), mad_half<true>(pair, r, c), f);
+    }
+    static __device__ __forceinline__ uint32_t mark(uint32_t v0, uint32_t v1, FT r, FT z, const F& f) {
+        if constexpr (SMALL) {
+            const uint32_t c = r + z;
+            return mark_small(mad_half<false>(v0, r, c), mad_half<false>(v1, r, c), f);
+        } else if constexpr (N <= 32) {
+            const uint64_t c = add_wide(r, z);
+            const uint64_t D = mad_u64_u32(v0, r, c) - mad_u64_u32(v1, r, c);
+            const uint32_t k = (uint32_t)D * f.pinv32();
+            if constexpr (N <= 31)
+                return (uint32_t)((uint64_t)((int64_t)(int32_t)k * (int32_t)(0u - f.p) + (int64_t)D) >> 32);
+            else
+                return (uint32_t)((uint64_t)((int64_t)(int32_t)k * (int32_t)(0u - f.p) + (int64_t)D) >> 32) ^ k;
+        } else if constexpr (F::kDefault) {
+            const uint32_t r0 = (uint32_t)r, r1 = 0u - (uint32_t)(r >> 32);
+            const uint64_t c2 = (r + z) << 1;
+            const uint64_t U = message2(v0, r0, r1, c2) - message2(v1, r0, r1, c2);
+            const int32_t k = (int32_t)((uint32_t)U * f.pinv32() << 24) >> 24;
+            const uint64_t e = (uint64_t)((int64_t)k * 9 + (int64_t)U);
+            return (uint32_t)e | ((uint32_t)(e >> 32) ^ (uint32_t)(2 * k));
+        } else {
+            const FT w0 = f.mul_add((FT)v0 + 1, r, z), w1 = f.mul_add((FT)v1 + 1, r, z);
+            return (uint32_t)(w0 ^ w1) | (uint32_t)((w0 ^ w1) >> 32);
+        }
+    }
+    // N = 33: twice the message v r + c, with r1 = -(r >> 32) as a mask.
+    static __device__ __forceinline__ uint64_t message2(uint32_t v, uint32_t r0, uint32_t r1, uint64_t c2) {
+        const uint64_t x = mad_u64_u32(v, r0, 0);
+        return mad_u64_u32((uint32_t)x, 2u, mad_u64_u32(v & r1, 9u, mad_u64_u32((uint32_t)(x >> 32), 9u, c2)));
+    }
+};
+
+// The minimum of a slot loop's marks in slot order, two slots to one
+// three-operand minimum (j compile-time after unrolling).
+template <int N>
+struct LeastMark {
+    uint32_t least = 0xFFFFFFFFu, last = 0;
+    __device__ __forceinline__ void take(int j, uint32_t mark) {
+        if (j % 2 == 0 && j < N - 1)
+            last = mark;
+        else
+            least = min3_in_order(least, j % 2 == 0 ? mark : last, mark);
+    }
+};
+
+// ------------------------------------------------------- windows as pairs
+//
+// For N <= 16 (p < 2^16) both parties' values of one window position fit in
+// one 32-bit word, P0's v_0 in the low half and P1's v_1 in the high half,
+// and the shuffle moves these words themselves, as the message array it
+// permutes.  Position i is then computed when i is known at compile time:
+// windows are constant shifts of both shares at once (v_pk_lshrrev_b16 on a
+// word that packs 16 bits of each), u_{l_x+1} = 0 needs no flag, and the slot
+// loop reads one word per slot.
+typedef uint16_t half2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ half2 as_half2(uint32_t w) { return __builtin_bit_cast(half2, w); }
+__device__ __forceinline__ uint32_t as_word(half2 h) { return __builtin_bit_cast(uint32_t, h); }
+
+template <int N>
+constexpr bool kPairs = N <= 16;
+
+template <typename T, int N>
+struct PairWindows {
+    static constexpr int LX = N - 1;
+    static constexpr int PER = 17 - LX;                       // positions in one packed word
+    static constexpr uint32_t WIN2 = ((1u << LX) - 1) * 0x10001u;
+    T a, b;                                                   // the flipped shares, shifted down by k_lo
+    half2 minus;                                              // (-2, -1), the parties' constants
+    half2 next;                                               // position k of the coming value()
+
+    __device__ __forceinline__ PairWindows(T a0k, T nb1k, uint32_t c) : a(a0k), b(nb1k), minus(as_half2(c)) {
+        next = window(0);
+    }
+    // Bits [k, k + l_x) of both shares, with other bits above; even positions
+    // carry the parties' constants (every adjacent sum takes exactly one).
+    __device__ __forceinline__ half2 window(int k) const {
+        const int off = k / PER * PER;
+        const half2 w = as_half2(__builtin_amdgcn_perm((uint32_t)(b >> off), (uint32_t)(a >> off), 0x05040100u));
+        const half2 m = w >> (half2)(uint16_t)(k - off);
+        return k % 2 == 0 ? m + minus : m;
+    }
+    // (v_0, v_1) of position k; called for k = 0, 1, ..., l_x in this order.
+    __device__ __forceinline__ uint32_t value(int k) {
+        half2 sum = next;
+        if (k < LX) {
+            next = window(k + 1);
+            sum += next;
+        } else if (k % 2 != 0) {
+            sum += minus;                                     // u_{l_x+1} = 0
+        }
+        return as_word(sum) & WIN2;
+    }
+};
+
+// All ones when t = 1, else zero, in the share width.
+template <typename T>
+__device__ __forceinline__ T spread(uint32_t t) {
+    const uint32_t w = 0u - t;
+    if constexpr (sizeof(T) == 8)
+        return join64(w, w);
+    else
+        return w;
+}
+
+// m ? a : b for m all ones or zero, as bit selects (v_bfi_b32).  A select on
+// a condition compiles to runs of v_cndmask_b32 on VCC, which issue at 22
+// cycles each on gfx950 when they follow each other.
+template <typename T>
+__device__ __forceinline__ T select_bits(T m, T a, T b) {
+    return (m & a) | (~m & b);
+}
+
+// (-1)^t v mod 2^l for v < 2^l (Alg. 7's flip): (v ^ -t) + t.
 template <typename T>
 __device__ __forceinline__ T flip_by(T v, uint32_t t, T mask) {
-    return t ? (T)((T)0 - v) & mask : v;
+    return (T)((v ^ spread<T>(t)) + (T)t) & mask;
 }
 
 // The shares a DReLU/ReLU works on, from the loaded ones: with k_in > 0 the
@@ -234,9 +325,9 @@ __device__ __forceinline__ void input_shares(T x0, T x1, T mask, T in_mask, uint
 // mask at the end reduces mod 2^l.
 template <typename T>
 __device__ __forceinline__ void drelu_finish(T dp, T rho, uint32_t t, T mask, T& y0, T& y1) {
-    const T tm = (T)0 - (T)t;
+    const T tm = spread<T>(t);
     y0 = (T)((rho ^ tm) + (T)(2 * t)) & mask;          // t = 1: ~rho + 2 = 1 - rho
-    y1 = (T)(((T)(dp - rho) ^ tm) - tm) & mask;
+    y1 = (T)(((T)(dp - rho) ^ tm) + (T)t) & mask;
 }
 
 // Alg. 8's preprocessing draws of element g: [a]_0, [b]_0, [c]_0 from
@@ -265,8 +356,9 @@ __device__ __forceinline__ void relu_finish(T dp, T in0, T in1, T ba0, T bb0, T 
     const T dd = (T)((in0 - ba0) + (in1 - ba1)) & mask;           // P0, P1: d = x - a
     const T m0 = (T)(dd * ee + dd * bb0 + ee * ba0 + bc0) & mask; // de + d[b] + e[a] + [c]
     const T m1 = (T)(dd * bb1 + ee * ba1 + bc1) & mask;
-    y0 = t ? (T)(in0 - m0) & mask : m0;                            // t[x] + (1 - 2t)[x D']
-    y1 = t ? (T)(in1 - m1) & mask : m1;
+    const T tm = spread<T>(t);
+    y0 = select_bits<T>(tm, (T)(in0 - m0) & mask, m0);              // t[x] + (1 - 2t)[x D']
+    y1 = select_bits<T>(tm, (T)(in1 - m1) & mask, m1);
 }
 
 // The flip bit t and the shuffle of one element, both from seed_01 (Alg. 7).
@@ -277,20 +369,45 @@ __device__ __forceinline__ void relu_finish(T dp, T in0, T in1, T ba0, T bb0, T 
 // 2 (c % 2) and 2 (c % 2) + 1 of block c / 2, low word first); a chunk takes
 // digits in order while the product of their radices stays <= 2^32, and a
 // digit of radix m is the part of F m above 2^64, F m mod 2^64 the next F.
+//
+// The kernels cut the digits of a chunk group by group: with M the product of
+// a group's radices, X = floor(F M / 2^64) holds its digits (mixed radix,
+// first digit most significant) and F M mod 2^64 is the next F.  With
+// C = ceil(2^32 / M), f = X C is X / M as a 32-bit fraction, too large by less
+// than 1 / M when (M - 1) (C M - 2^32) < 2^32, so the digits of f are those of
+// X: digit of radix m = the high word of f m, the low word the next f.  That
+// is one multiply a digit after four operations a group, where cutting each
+// digit from the 64-bit F takes two multiplies and a move: N = 19 runs its 19
+// digits in 4 groups.
 template <int N>
 struct ShufflePlan {
-    int chunk[N];      // the chunk of digit k
-    constexpr ShufflePlan() : chunk() {
-        uint64_t prod = 1;
-        int c = 0;
+    int chunk[N];          // the chunk of digit k
+    bool group[N];         // digit k is the first of a group
+    uint32_t prod[N];      // the product of the radices of the group that starts at k
+    static constexpr uint64_t radix(int k) { return k == 0 ? 2 : (uint64_t)k + 1; }
+    static constexpr uint64_t scale(uint64_t m) { return ((1ull << 32) + m - 1) / m; }
+    static constexpr bool fits(uint64_t m) {
+        return m < (1ull << 32) && (m - 1) * scale(m) < (1ull << 32) && (m - 1) * (scale(m) * m - (1ull << 32)) < (1ull << 32);
+    }
+    constexpr ShufflePlan() : chunk(), group(), prod() {
+        uint64_t prod_c = 1, prod_g = 1;
+        int c = 0, g = 0;
         for (int k = 0; k < N; ++k) {
-            const uint64_t m = k == 0 ? 2 : (uint64_t)k + 1;
-            if (prod * m > (1ull << 32)) {
+            const uint64_t m = radix(k);
+            const bool next = prod_c * m > (1ull << 32);
+            if (next) {
                 ++c;
-                prod = 1;
+                prod_c = 1;
             }
-            prod *= m;
+            if (k == 0 || next || !fits(prod_g * m)) {
+                g = k;
+                prod_g = 1;
+            }
+            prod_c *= m;
+            prod_g *= m;
             chunk[k] = c;
+            group[k] = g == k;
+            prod[g] = (uint32_t)prod_g;
         }
     }
 };
@@ -302,82 +419,112 @@ struct ShufflePlan {
 // address of a drawn index j is one multiply-add.  With E = 4 the 64 lanes of
 // a wave touch 64 different banks whatever their k; E = 4 while 8 blocks of N
 // rows fit the compute unit's 160 KiB of LDS (N <= 20), else E = 2.  Byte 0
-// of an entry is the window position; its top byte is the width of the
-// slot's next window u_{i+1}: 0 for the slot that received the top position
+// of an entry is the window position; its top byte is the slot's factor of
+// the window sum (window_sum): 2 for the slot that received the top position
 // l_x (u_{l_x+1} is 0; the last swap puts it at slot j_{N-1}, and nothing
-// moves it after) and l_x for every other slot (shuffle_next_width).  The
-// slice stays valid until the thread's next call.
+// moves it after) and 3 for every other slot (ShuffledPositions).  The slice
+// stays valid until the thread's next call.
 template <int N>
 struct ShuffleSlice {
     static constexpr int E = N <= 20 ? 4 : 2;               // bytes per entry
     static constexpr int ROW = 256 * E;
     using U = typename std::conditional<E == 4, uint32_t, uint16_t>::type;
-    static constexpr U FLAG = (U)((U)(N - 1) << (8 * (E - 1)));  // top byte of a slot below l_x
+    static constexpr U entry(int k) { return (U)((U)(k == N - 1 ? 2 : 3) << (8 * (E - 1)) | (U)k); }
 };
 
+// The digits of the plan in order: t, then j_1, j_2, ... (k compile-time after
+// unrolling).
 template <int N>
-__device__ __forceinline__ uint8_t* shuffle_fill(const StreamAt& r01, uint32_t& t) {
-    using S = ShuffleSlice<N>;
-    using U = typename S::U;
-    constexpr ShufflePlan<N> plan{};
-    __shared__ U lds[N * 256];
-    uint8_t* A = reinterpret_cast<uint8_t*>(lds + threadIdx.x);
+struct ShuffleDigits {
+    const StreamAt& r01;
     Words4 w = {0, 0, 0, 0};
-    uint32_t lo = 0, hi = 0;
-#pragma unroll
-    for (int k = 0; k < N; ++k) {
+    uint32_t lo = 0, hi = 0;     // the chunk's F
+    uint32_t f = 0;              // the group's fraction
+
+    __device__ __forceinline__ explicit ShuffleDigits(const StreamAt& r) : r01(r) {}
+    __device__ __forceinline__ uint32_t digit(int k) {
+        constexpr ShufflePlan<N> plan{};
         const int c = plan.chunk[k];
         if (k == 0 || plan.chunk[k > 0 ? k - 1 : 0] != c) {
             if (c % 2 == 0) w = r01.block(TAG_SHUFFLE, (uint32_t)(c / 2));
             lo = c % 2 ? w.w2 : w.w0;
             hi = c % 2 ? w.w3 : w.w1;
         }
-        const uint32_t m = k == 0 ? 2u : (uint32_t)k + 1u;
-        const uint64_t pl = (uint64_t)lo * m;
-        const uint64_t ph = (uint64_t)hi * m + (uint32_t)(pl >> 32);
-        lo = (uint32_t)pl;
-        hi = (uint32_t)ph;
-        uint32_t d = (uint32_t)(ph >> 32);                    // t, or j_k <= k
-        if (k == 0) {
-            t = d;
-            *reinterpret_cast<U*>(A) = N == 1 ? (U)0 : S::FLAG;  // A[0] = 0
-        } else {
-            // d as a register of its own: the entry's address is then one
-            // shift-add, where the compiler would otherwise cut d * ROW out
-            // of the 64-bit product with an alignbit and a mask
-            asm("" : "+v"(d));
-            U* aj = reinterpret_cast<U*>(A + d * S::ROW);
-            *reinterpret_cast<U*>(A + k * S::ROW) = *aj;        // A[k] = A[j_k]
-            *aj = k == N - 1 ? (U)k : (U)(S::FLAG | (U)k);      // A[j_k] = k
+        if (plan.group[k]) {
+            const uint32_t M = plan.prod[k];
+            const uint64_t pl = (uint64_t)lo * M;
+            const uint64_t ph = (uint64_t)hi * M + (uint32_t)(pl >> 32);
+            lo = (uint32_t)pl;
+            hi = (uint32_t)ph;
+            f = (uint32_t)(ph >> 32) * (uint32_t)ShufflePlan<N>::scale(M);
         }
+        const uint32_t m = (uint32_t)ShufflePlan<N>::radix(k);
+        const uint64_t p = (m & (m - 1)) == 0 ? mul_wide_s(f, m) : (uint64_t)f * m;
+        f = (uint32_t)p;
+        uint32_t d = (uint32_t)(p >> 32);                     // t, or j_k <= k
+        // d as a register of its own: the entry's address is then one
+        // shift-add, where the compiler would otherwise cut d * ROW out
+        // of the 64-bit product with an alignbit and a mask
+        if (k > 0) asm("" : "+v"(d));
+        return d;
+    }
+};
+
+// The shuffle proper (digits j_1, ... still to come) over entries of type U,
+// entry(k) being the one of position k.
+template <int N, typename U, typename Entry>
+__device__ __forceinline__ uint8_t* shuffle_run(ShuffleDigits<N>& digits, Entry&& entry) {
+    __shared__ U lds[N * 256];
+    constexpr int ROW = 256 * (int)sizeof(U);
+    uint8_t* A = reinterpret_cast<uint8_t*>(lds + threadIdx.x);
+    *reinterpret_cast<U*>(A) = entry(0);                      // A[0] = 0
+#pragma unroll
+    for (int k = 1; k < N; ++k) {
+        U* aj = reinterpret_cast<U*>(A + digits.digit(k) * ROW);
+        *reinterpret_cast<U*>(A + k * ROW) = *aj;             // A[k] = A[j_k]
+        *aj = entry(k);                                       // A[j_k] = k
     }
     return A;
 }
 
-// The width of slot s's next window after shuffle_fill: l_x, or 0 for the
-// slot of position l_x (the entry's top byte).
+// A filled slice of window positions.  The factors are read through a
+// pointer of their own: with 2-byte entries the compiler would otherwise read
+// both bytes at once and take them apart again on the VALU.
 template <int N>
-__device__ __forceinline__ uint32_t shuffle_next_width(const uint8_t* A, uint32_t s) {
-    return A[s * ShuffleSlice<N>::ROW + ShuffleSlice<N>::E - 1];
-}
+struct ShuffledPositions {
+    typedef const __attribute__((address_space(3))) uint8_t LdsByte;
+    LdsByte* entries;
+    LdsByte* factors;
+    __device__ __forceinline__ explicit ShuffledPositions(const uint8_t* A)
+        : entries((LdsByte*)A), factors((LdsByte*)A + (ShuffleSlice<N>::E - 1)) {
+        if constexpr (ShuffleSlice<N>::E == 2) asm("" : "+v"(factors));
+    }
+    // Window position of slot s, and its factor of the window sum: 3, or 2 for
+    // position l_x.
+    __device__ __forceinline__ uint32_t pos(uint32_t s) const { return entries[s * ShuffleSlice<N>::ROW]; }
+    __device__ __forceinline__ uint32_t times(uint32_t s) const { return factors[s * ShuffleSlice<N>::ROW]; }
+};
 
-// Window position of slot s after shuffle_fill.
+// The shuffle of the window positions, after t was taken from the digits.
 template <int N>
-__device__ __forceinline__ uint32_t shuffle_pos(const uint8_t* A, uint32_t s) {
-    return A[s * ShuffleSlice<N>::ROW];
+__device__ __forceinline__ ShuffledPositions<N> shuffle_fill(ShuffleDigits<N>& digits) {
+    using S = ShuffleSlice<N>;
+    using U = typename S::U;
+    return ShuffledPositions<N>(shuffle_run<N, U>(digits, [](int k) { return S::entry(k); }));
 }
 
 // The shuffle as words: byte q of perm[k] is the position of slot 4k + q
 // (bytes past N zero).
 template <int N>
 __device__ __forceinline__ uint32_t shuffle_perm(const StreamAt& r01, uint32_t (&perm)[(N + 3) / 4]) {
-    uint32_t t;
-    const uint8_t* A = shuffle_fill<N>(r01, t);
+    ShuffleDigits<N> digits(r01);
+    const uint32_t t = digits.digit(0);
+    const ShuffledPositions<N> A = shuffle_fill<N>(digits);
 #pragma unroll
     for (int k = 0; k < (N + 3) / 4; ++k) {
         uint32_t v = 0;
 #pragma unroll
-        for (int q = 0; q < 4 && 4 * k + q < N; ++q) v |= shuffle_pos<N>(A, (uint32_t)(4 * k + q)) << (8 * q);
+        for (int q = 0; q < 4 && 4 * k + q < N; ++q) v |= A.pos((uint32_t)(4 * k + q)) << (8 * q);
         perm[k] = v;
     }
     return t;
@@ -389,8 +536,9 @@ __device__ __forceinline__ uint32_t shuffle_perm(const StreamAt& r01, uint32_t (
 //    2s + 1 (z of slot s) is the N-bit field at bits [N v, N v + N) of the
 //    stream, whose bit i is bit i % 32 of word i / 32, word w being word
 //    w % 4 of block w / 4; r = min(max(R, 1), p - 1), z = Z mod p.  Up to
-//    N = 24 the kernels keep both shifted left by SH = 32 - N, which the
-//    fields' mul_add_sh folds without a funnel shift.
+//    N = 31 the kernels keep both shifted left by SH = 32 - N: a field is then
+//    one v_alignbit_b32 of two stream words, whether it straddles them or
+//    not, and P2's test needs no shift back.
 //  * otherwise, p < 2^32: two slots to a block, words (0, 1) and (2, 3), by
 //    32-bit multiply-shift; p > 2^32: one slot per block, 64-bit words.
 template <int N, typename F>
@@ -399,27 +547,45 @@ struct MaskDraws {
     static constexpr bool STREAM = F::kDefault && N >= 17;
     static constexpr int SPB = WIDE ? 1 : 2;                                            // slots per block otherwise
     static constexpr int NB = STREAM ? (2 * N * N + 127) / 128 : (N + SPB - 1) / SPB;   // blocks per element
-    static constexpr int SH = STREAM && N <= 24 ? 32 - N : 0;                           // shift of the kept r and z
+    static constexpr int SH = STREAM && N <= 31 ? 32 - N : 0;                           // shift of the kept r and z
 };
 
 // r and z in the kept representation from the raw fields R, Z (STREAM,
-// already shifted left by SH).
+// already shifted left by SH).  z is left as the field, a value below 2^N
+// congruent to Z mod p (reduced_z finishes it where a message is stored).
 template <int N, typename F>
 __device__ __forceinline__ void stream_draws(typename F::T R, typename F::T Z, typename F::T& r,
                                              typename F::T& z) {
     using FT = typename F::T;
-    constexpr int SH = MaskDraws<N, F>::SH;
-    constexpr FT KEEP = (FT)~(((FT)1 << SH) - 1);
-    // r: clamp into Z_p^* (one v_med3); its low SH bits cleared, so that a
-    // product r s has zero low SH bits.  z keeps whatever bits R and Z carry
-    // below SH: an addend's low SH bits then stay below bit SH of a r + z
-    // and never reach the folded value, and a subtraction from it masks them
-    // first (reshare_neg).
-    r = min(max((FT)(R & KEEP), (FT)((FT)1 << SH)), (FT)((FT)(F::p - 1) << SH));
-    if constexpr (SH > 0 && F::p == (1ull << N) - 1)
-        z = Z;                                      // Mersenne: Z <= p already stands for Z mod p
-    else
-        z = min(Z, (FT)(Z - ((FT)F::p << SH)));     // Z mod p (Z < 2p; the low SH bits decide nothing)
+    z = Z;
+    if constexpr (MaskDraws<N, F>::WIDE) {
+        // r = min(max(R, 1), p - 1) for p = 2^33 - 9, word by word: with bit 32
+        // set the low word is at most 2^32 - 10, without it at least 1
+        const uint32_t r1 = (uint32_t)(R >> 32);
+        const uint32_t low = min((uint32_t)R, ~((0u - r1) & 9u));
+        r = join64(max(low, r1 ^ 1u), r1);
+    } else {
+        // clamp into Z_p^* (one v_med3); the low SH bits of r are cleared, so
+        // that a product r s has zero low SH bits.  z keeps whatever bits Z
+        // carries below SH: an addend's low SH bits stay below bit SH of
+        // a r + z and cancel in P2's difference, and a subtraction from z masks
+        // them first (reshare_neg).
+        constexpr int SH = MaskDraws<N, F>::SH;
+        constexpr FT KEEP = (FT)~(((FT)1 << SH) - 1);
+        r = min(max((FT)(R & KEEP), (FT)((FT)1 << SH)), (FT)((FT)(F::p - 1) << SH));
+    }
+}
+
+// A kept z (shifted by SH) as Z mod p, still shifted (a Mersenne Z = p may
+// stay: it stands for 0 and is a valid addend).
+template <int N, typename F>
+__device__ __forceinline__ typename F::T reduced_z(const F& f, typename F::T z) {
+    using FT = typename F::T;
+    using D = MaskDraws<N, F>;
+    if constexpr (D::STREAM) {
+        if constexpr (F::p != (FT)((1ull << N) - 1)) return min(z, (FT)(z - ((FT)F::p << D::SH)));
+    }
+    return z;
 }
 
 // Slot H's r and z of mask block w without STREAM (H < SPB, compile-time).
@@ -469,7 +635,7 @@ struct MaskReader {
             return __builtin_amdgcn_alignbit(word(k + 1, b), word(k, b), s);
         } else if constexpr (D::WIDE) {
             const int k = o / 32, s = o % 32;       // 33 bits: always two words
-            return (join64(word(k, b), word(k + 1, b)) >> s) & ((1ull << N) - 1);
+            return join64(__builtin_amdgcn_alignbit(word(k + 1, b), word(k, b), s), (word(k + 1, b) >> s) & 1u);
         } else {
             const int k = o / 32, s = o % 32;
             constexpr uint32_t M = N >= 32 ? ~0u : (1u << N) - 1;
@@ -505,7 +671,8 @@ __device__ __forceinline__ typename F::T stream_field_at(const uint32_t* W, uint
         return __builtin_amdgcn_alignbit(W[k + 1], W[k], (uint32_t)lo & 31u);   // low SH bits as they come
     } else if constexpr (D::WIDE) {
         const int k = o >> 5;
-        return (join64(W[k], W[k + 1]) >> (o & 31)) & ((1ull << N) - 1);
+        const uint32_t s = (uint32_t)o & 31u;
+        return join64(__builtin_amdgcn_alignbit(W[k + 1], W[k], s), (W[k + 1] >> s) & 1u);
     } else {
         const int k = o >> 5;
         constexpr uint32_t M = N >= 32 ? ~0u : (1u << N) - 1;
@@ -513,14 +680,16 @@ __device__ __forceinline__ typename F::T stream_field_at(const uint32_t* W, uint
     }
 }
 
-// Plain canonical values of kept draws (the record of the precomputed mode).
+// Plain canonical values of kept draws (captured messages, the record of the
+// precomputed mode).
 template <int N, typename F>
 __device__ __forceinline__ void plain_draws(const F& f, typename F::T& r, typename F::T& z) {
-    constexpr int SH = MaskDraws<N, F>::SH;
-    if constexpr (SH > 0) {
-        r >>= SH;
-        z >>= SH;
-        z = min(z, z - f.p);                        // a Mersenne Z = p stands for 0
+    using D = MaskDraws<N, F>;
+    if constexpr (D::STREAM) {
+        using FT = typename F::T;
+        r >>= D::SH;
+        z >>= D::SH;
+        z = min(z, (FT)(z - f.p));
     }
 }
 
@@ -538,34 +707,49 @@ __device__ __forceinline__ T drelu_round1(T in0, T n1, uint64_t g, T mask, uint3
     constexpr bool WIDE = std::is_same<FT, uint64_t>::value;
     static_assert(WIDE == (N == 33), "64-bit field elements exactly when l_x = 32");
 
-    // The flip bit t and the shuffle, both from seed_01.
     const StreamAt r01 = s01.at(g);
-    uint32_t t;
-    const uint8_t* A = shuffle_fill<N>(r01, t);
+    using Test = SlotTest<N, F, MaskDraws<N, F>::SH>;
+    LeastMark<N> p2;
+    MaskReader<N, F> masks;
+    ShuffleDigits<N> digits(r01);
+    const uint32_t t = digits.digit(0);
+    t_out = t;
 
     // Flip: [x] := (-1)^t [x]  (both parties); P1 cuts its negated share
-    // -(-1)^t [x]_1 = (-1)^t n1.
-    const T a0 = flip_by(in0, t, mask);
-    const T nb1 = flip_by(n1, t, mask);
-    const T a0k = a0 >> k_lo, nb1k = nb1 >> k_lo;         // common low cut of every window
+    // -(-1)^t [x]_1 = (-1)^t n1.  Then the common low cut of every window.
+    const T a0k = flip_by(in0, t, mask) >> k_lo, nb1k = flip_by(n1, t, mask) >> k_lo;
 
-    FT least = f.p;                                        // P2: min over slots of w0 + w1 mod p
-    MaskReader<N, F> masks;
+    if constexpr (kPairs<N> && !CAP) {
+        PairWindows<T, N> win(a0k, nb1k, in_vgpr(0xFFFFFFFEu));
+        const uint8_t* A = shuffle_run<N, uint32_t>(digits, [&](int k) { return win.value(k); });
 #pragma unroll
-    for (int j = 0; j < N; ++j) {
-        // Mask r and reshare z of slot j.
-        FT r, z;
-        masks.slot(r01, j, f, r, z);
-        FT w0, w1;
-        slot_messages<T, N, F, MaskDraws<N, F>::SH, !CAP>(a0k, nb1k, shuffle_pos<N>(A, j), shuffle_next_width<N>(A, j), r, z,
-                                                          f, w0, w1, least);
-        if constexpr (CAP) {
-            cap[e * N + j] = w0;
-            cap[(ncap + e) * N + j] = w1;
+        for (int j = 0; j < N; ++j) {
+            FT r, z;
+            masks.slot(r01, j, f, r, z);
+            p2.take(j, Test::mark_pair(*reinterpret_cast<const uint32_t*>(A + j * 1024), r, z, f));
+        }
+    } else {
+        const ShuffledPositions<N> A = shuffle_fill<N>(digits);
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            FT r, z;
+            masks.slot(r01, j, f, r, z);
+            uint32_t v0, v1;
+            window_sums<T, N>(a0k, nb1k, A.pos(j), A.times(j), v0, v1);
+            if constexpr (CAP) {
+                FT w0, w1;
+                plain_draws<N, F>(f, r, z);
+                slot_messages<F>(v0, v1, r, z, f, w0, w1);
+                cap[e * N + j] = w0;
+                cap[(ncap + e) * N + j] = w1;
+                const FT w = addmod(w0, w1, f);                // P2 reconstructs and tests
+                p2.take(j, w == 0 ? 0u : 0xFFFFFFFFu);
+            } else {
+                p2.take(j, Test::mark(v0, v1, r, z, f));
+            }
         }
     }
-    t_out = t;
-    return least == 0 ? 1 : 0;                             // D' = [some slot is 0]
+    return p2.least <= Test::LIMIT ? 1 : 0;                // D' = [some slot is 0]
 }
 
 // One element, all three parties.  N = l_x + 1 windows, fixed at compile
@@ -720,24 +904,23 @@ __device__ __forceinline__ void drelu_element_group(const T* __restrict__ X0, co
                                                     const Stream& s02, const Stream& s12, const F& f) {
     using FT = typename F::T;
     using D = MaskDraws<N, F>;
-    constexpr bool WIDE = D::WIDE;
     constexpr int SPB = D::SPB;                             // slots per mask block without STREAM
-    constexpr int SH = D::SH;
     constexpr int NB = D::NB;                               // mask blocks
     constexpr int ROUNDS = (NB + G - 1) / G;
 
     T in0, n1;
     input_shares<T>(ld_nt(&X0[e]), ld_nt(&X1[e]), mask, in_mask, k_in, in0, n1);
 
+    using Test = SlotTest<N, F, D::SH>;
     const StreamAt r01 = s01.at(g);
-    uint32_t t;
-    const uint8_t* A = shuffle_fill<N>(r01, t);
+    ShuffleDigits<N> digits(r01);
+    const uint32_t t = digits.digit(0);
+    const ShuffledPositions<N> A = shuffle_fill<N>(digits);
 
-    const T a0 = flip_by(in0, t, mask);                  // the flip, as in drelu_round1
-    const T nb1 = flip_by(n1, t, mask);
-    const T a0k = a0 >> k_lo, nb1k = nb1 >> k_lo;
+    const T a0k = flip_by(in0, t, mask) >> k_lo;         // the flip, as in drelu_round1
+    const T nb1k = flip_by(n1, t, mask) >> k_lo;
 
-    FT least = f.p;
+    uint32_t least = 0xFFFFFFFFu;
     if constexpr (D::STREAM) {
         // The group's 4 NB stream words, with a zero word on either side.
         constexpr int STRIDE = 4 * NB + 2;
@@ -766,10 +949,10 @@ __device__ __forceinline__ void drelu_element_group(const T* __restrict__ X0, co
             const uint32_t js = valid ? j : 0u;             // past the last slot: any slot, not counted
             FT r, z;
             stream_draws<N, F>(stream_field_at<N, F>(W, 2 * js), stream_field_at<N, F>(W, 2 * js + 1), r, z);
-            FT w0, w1, v = f.p;
-            slot_messages<T, N, F, SH, true>(a0k, nb1k, shuffle_pos<N>(A, js), shuffle_next_width<N>(A, js), r, z, f, w0, w1,
-                                             v);
-            least = (valid && v < least) ? v : least;
+            uint32_t v0, v1;
+            window_sums<T, N>(a0k, nb1k, A.pos(js), A.times(js), v0, v1);
+            const uint32_t u = Test::mark(v0, v1, r, z, f);
+            least = (valid && u < least) ? u : least;
         }
         wave_sync();                                        // every read before the next element's words
     } else {
@@ -782,30 +965,25 @@ __device__ __forceinline__ void drelu_element_group(const T* __restrict__ X0, co
                 // slot j = SPB * blk + h (past the last slot: any slot, its message is not counted)
                 const bool valid = SPB * blk + h < (uint32_t)N;
                 const uint32_t js = valid ? SPB * blk + h : 0u;
-                const uint32_t pos = shuffle_pos<N>(A, js);
+                const uint32_t pos = A.pos(js);
                 FT r, z;
                 if (h == 0)
                     block_draws<N, F, 0>(w, f, r, z);
                 else
                     block_draws<N, F, (SPB > 1 ? 1 : 0)>(w, f, r, z);
-                FT w0, w1, v = f.p;
-                slot_messages<T, N, F, SH, true>(a0k, nb1k, pos, shuffle_next_width<N>(A, js), r, z, f, w0, w1, v);
-                least = (valid && v < least) ? v : least;
+                uint32_t v0, v1;
+                window_sums<T, N>(a0k, nb1k, pos, A.times(js), v0, v1);
+                const uint32_t u = Test::mark(v0, v1, r, z, f);
+                least = (valid && u < least) ? u : least;
             }
         }
     }
 #pragma unroll
     for (int o = 1; o < G; o <<= 1) {
-        if constexpr (WIDE) {
-            const uint32_t lo = __shfl_xor((uint32_t)least, o, G), hi = __shfl_xor((uint32_t)(least >> 32), o, G);
-            const FT other = join64(lo, hi);
-            least = other < least ? other : least;
-        } else {
-            const FT other = (FT)__shfl_xor((uint32_t)least, o, G);
-            least = other < least ? other : least;
-        }
+        const uint32_t other = __shfl_xor(least, o, G);
+        least = other < least ? other : least;
     }
-    const T dp = least == 0 ? 1 : 0;
+    const T dp = least <= Test::LIMIT ? 1 : 0;
 
     T y0, y1;
     if constexpr (!RELU) {
@@ -854,9 +1032,9 @@ __global__ BC_KERNEL_ATTRS void k_drelu_group(DreluKArgs A, F f_arg) {
 }
 
 // Host helpers: field parameters for each prime size.
-inline FieldSmall make_field_small(uint64_t p) { return FieldSmall{(uint32_t)p, 1.0f / (float)p}; }
-inline Field24 make_field24(uint64_t p) { return Field24{(uint32_t)p, (double)p, 1.0 / (double)p}; }
-inline Field32 make_field32(uint64_t p) { return Field32{(uint32_t)p, UINT64_MAX / p}; }
+inline FieldSmall make_field_small(uint64_t p) { return FieldSmall{(uint32_t)p, 1.0f / (float)p, inverse32((uint32_t)p)}; }
+inline Field24 make_field24(uint64_t p) { return Field24{(uint32_t)p, (double)p, 1.0 / (double)p, inverse32((uint32_t)p)}; }
+inline Field32 make_field32(uint64_t p) { return Field32{(uint32_t)p, UINT64_MAX / p, inverse32((uint32_t)p)}; }
 inline Field64 make_field64(uint64_t p) { return Field64{p, (double)p, 1.0 / (double)p}; }
 
 inline DreluKArgs make_kargs(const DreluLaunch& L) {

@@ -139,7 +139,8 @@ __device__ __forceinline__ void drelu_pre_element(const T* __restrict__ X0, cons
     const T a0 = flip_by(in0, t, mask);                // the flip, as in drelu_round1
     const T nb1 = flip_by(n1, t, mask);
     const T a0k = a0 >> k_lo, nb1k = nb1 >> k_lo;
-    FT least = f.p;
+    using Test = SlotTest<N, F, 0>;
+    LeastMark<N> p2;
     constexpr int K = RzLayout<N>::K;
     uint64_t cur = 0;                                  // the word being read
 #pragma unroll
@@ -153,14 +154,20 @@ __device__ __forceinline__ void drelu_pre_element(const T* __restrict__ X0, cons
         }
         const FT r = rv[0], z = rv[1];
         const uint32_t pos = (perm[j >> 2] >> (8 * (j & 3))) & 63u;
-        FT w0, w1;
-        slot_messages<T, N, F, 0, !CAP>(a0k, nb1k, pos, r, z, f, w0, w1, least);
+        uint32_t v0, v1;
+        window_sums<T, N>(a0k, nb1k, pos, v0, v1);
         if constexpr (CAP) {
+            FT w0, w1;
+            slot_messages<F>(v0, v1, r, z, f, w0, w1);
             cap[e * N + j] = w0;
             cap[(n + e) * N + j] = w1;
+            const FT w = addmod(w0, w1, f);
+            p2.take(j, w == 0 ? 0u : 0xFFFFFFFFu);
+        } else {
+            p2.take(j, Test::mark(v0, v1, r, z, f));
         }
     }
-    const T dp = least == 0 ? 1 : 0;
+    const T dp = p2.least <= Test::LIMIT ? 1 : 0;
     T y0, y1;
     if constexpr (!RELU) {
         const Words4 w = s02.block(g, TAG_RESP, 0);                 // rho, regenerated from seed_02

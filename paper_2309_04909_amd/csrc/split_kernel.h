@@ -28,26 +28,19 @@ struct SplitKArgs {
     Stream s01, s02;
 };
 
-// One party's message for one slot (the P0 or P1 half of slot_messages).
-// ak: the party's flipped share (P1: its negation) shifted down by k_lo; r
-// and z in the kept representation of MaskDraws (shifted left by SH).
+// One party's message for one slot in [0, p) (the P0 or P1 half of the fused
+// kernel's slot).  ak: the party's flipped share (P1: its negation) shifted
+// down by k_lo; r and z in the kept representation of MaskDraws (shifted
+// left by SH).
 template <typename T, int N, typename F, int PARTY, int SH = MaskDraws<N, F>::SH>
-__device__ __forceinline__ typename F::T party_message(T ak, uint32_t pos, typename F::T r, typename F::T z,
-                                                       const F& f) {
+__device__ __forceinline__ typename F::T party_message(T ak, uint32_t pos, uint32_t times, typename F::T r,
+                                                       typename F::T z, const F& f) {
     using FT = typename F::T;
-    constexpr int LX = N - 1;
-    constexpr FT TWO_LX = (FT)1 << LX;
-    constexpr FT WIN = TWO_LX - 1;
-    const FT Wv = window<T, N, FT>(ak, pos);
-    const FT more = (FT)(int64_t)((int32_t)(pos - (uint32_t)LX) >> 31);
-    const FT un = (Wv >> 1) & more;                                   // u_{i+1}, u_{l_x+1} := 0
-    if constexpr (PARTY == 0) {
-        const FT s0 = ((Wv + un - 2) & WIN) + 1;                     // v0, or 2^l_x when v0 = 0
-        return field_mul_add<SH>(f, s0, r, z);
-    } else {
-        const FT s1 = (f.p - 1) - ((Wv + un - 1) & WIN);             // v1 + p - 2^l_x, v1 = -(Wv + un)
-        return field_mul_add<SH>(f, s1, r, reshare_neg<SH>(f, z));
-    }
+    z = reduced_z<N, F>(f, z);
+    if constexpr (PARTY == 0)                                            // s_0 = v_0 + 1
+        return field_mul_add<SH>(f, (FT)window_sum<T, N, 2>(ak, pos, times) + 1, r, z);
+    else                                                                 // s_1 = p - (v_1 + 1)
+        return field_mul_add<SH>(f, (FT)((f.p - 1) - window_sum<T, N, 1>(ak, pos, times)), r, reshare_neg<SH>(f, z));
 }
 
 template <int N>
@@ -85,8 +78,9 @@ __global__ BC_KERNEL_ATTRS void k_send(SplitKArgs A, F f_arg) {
         const uint64_t g = A.elem_base + e;
         const T x = X[e] & mask;
         const StreamAt r01 = A.s01.at(g);
-        uint32_t t;
-        const uint8_t* sig = shuffle_fill<N>(r01, t);
+        ShuffleDigits<N> digits(r01);
+        const uint32_t t = digits.digit(0);
+        const ShuffledPositions<N> sig = shuffle_fill<N>(digits);
         // the flipped share (-1)^t x; P1 cuts its negation (-1)^(t+1) x
         const T ak = flip_by(x, PARTY == 0 ? t : t ^ 1u, mask) >> A.k_lo;
         uint32_t words[W];
@@ -97,7 +91,7 @@ __global__ BC_KERNEL_ATTRS void k_send(SplitKArgs A, F f_arg) {
         for (int j = 0; j < N; ++j) {
             FT r, z;
             masks.slot(r01, j, f, r, z);
-            pack_slot<N>(words, j, (uint64_t)party_message<T, N, F, PARTY>(ak, shuffle_pos<N>(sig, j), r, z, f));
+            pack_slot<N>(words, j, (uint64_t)party_message<T, N, F, PARTY>(ak, sig.pos(j), sig.times(j), r, z, f));
         }
 #pragma unroll
         for (int k = 0; k < W; ++k) st_nt(&M[(uint64_t)k * A.n + e], words[k]);

@@ -32,7 +32,7 @@ __device__ __forceinline__ void tile_elements(const T* X0, const T* X1, T* Y0, T
         const uint32_t in = i + blockDim.x;
         const T a0n = load_buf<T>(B0, in), a1n = load_buf<T>(B1, in);
         T y0, y1;
-        drelu_element_of<T, N, F, RELU, false>(a0, a1, y0, y1, nullptr, 0, e0 + i, base + e0 + i, mask, in_mask, k_in,
+        drelu_element_of<T, N, F, RELU, false>(a0, a1, y0, y1, nullptr, 0, e0 + i, Index::of(base + e0, i), mask, in_mask, k_in,
                                                k_lo, s01, s02, s12, f);
         store_at(Y0 + e0, i, y0);
         store_at(Y1 + e0, i, y1);
@@ -80,24 +80,29 @@ __device__ __forceinline__ void batch_walk(const bc_segment* __restrict__ segs,
         // the segment's input ring l + k_in (Alg. 5 by k_in first; 0 = the plain load)
         const uint32_t k_in = S.k_in, lin = A.ell + k_in;
         const T in_mask = lin >= 8 * sizeof(T) ? (T)~(T)0 : (T)(((T)1 << lin) - 1);
-        if (S.rand) {
-            // precomputed randomness: the segment's record replaces its seed_01
-            // draws (and holds P2's [c]_1); seed_02 / seed_12 draws are regenerated
-            const bool relu = S.op == BC_OP_RELU;
-            const RecordView<T> R = record_view<T>(S.rand, (uint32_t)N, relu, S.n);
-            if (relu) {
-                for (uint64_t e = e0 + threadIdx.x; e < e1; e += blockDim.x)
-                    drelu_pre_element<T, N, F, true, false>(X0, X1, Y0, Y1, nullptr, R, e, base + e, mask, in_mask,
-                                                            k_in, A.k_lo, s02, s12, f);
+        // the tile's elements, in two parts where their global index passes a
+        // multiple of 2^32
+        for (uint64_t b0 = e0, b1; b0 < e1; b0 = b1) {
+            b1 = index_end(base, b0, e1);
+            if (S.rand) {
+                // precomputed randomness: the segment's record replaces its seed_01
+                // draws (and holds P2's [c]_1); seed_02 / seed_12 draws are regenerated
+                const bool relu = S.op == BC_OP_RELU;
+                const RecordView<T> R = record_view<T>(S.rand, (uint32_t)N, relu, S.n);
+                if (relu) {
+                    for (uint64_t e = b0 + threadIdx.x; e < b1; e += blockDim.x)
+                        drelu_pre_element<T, N, F, true, false>(X0, X1, Y0, Y1, nullptr, R, e, Index::of(base + b0, e - b0),
+                                                                mask, in_mask, k_in, A.k_lo, s02, s12, f);
+                } else {
+                    for (uint64_t e = b0 + threadIdx.x; e < b1; e += blockDim.x)
+                        drelu_pre_element<T, N, F, false, false>(X0, X1, Y0, Y1, nullptr, R, e, Index::of(base + b0, e - b0),
+                                                                 mask, in_mask, k_in, A.k_lo, s02, s12, f);
+                }
+            } else if (S.op == BC_OP_RELU) {
+                tile_elements<T, N, F, true>(X0, X1, Y0, Y1, b0, b1, base, mask, in_mask, k_in, A.k_lo, s01, s02, s12, f);
             } else {
-                for (uint64_t e = e0 + threadIdx.x; e < e1; e += blockDim.x)
-                    drelu_pre_element<T, N, F, false, false>(X0, X1, Y0, Y1, nullptr, R, e, base + e, mask, in_mask,
-                                                             k_in, A.k_lo, s02, s12, f);
+                tile_elements<T, N, F, false>(X0, X1, Y0, Y1, b0, b1, base, mask, in_mask, k_in, A.k_lo, s01, s02, s12, f);
             }
-        } else if (S.op == BC_OP_RELU) {
-            tile_elements<T, N, F, true>(X0, X1, Y0, Y1, e0, e1, base, mask, in_mask, k_in, A.k_lo, s01, s02, s12, f);
-        } else {
-            tile_elements<T, N, F, false>(X0, X1, Y0, Y1, e0, e1, base, mask, in_mask, k_in, A.k_lo, s01, s02, s12, f);
         }
     }
 }

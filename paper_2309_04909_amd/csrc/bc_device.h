@@ -100,17 +100,37 @@ __device__ __forceinline__ void launder_key(uint32_t& a, uint32_t& c) {
     asm volatile("" : "+s"(a), "+s"(c));
 }
 
+// Global element index.  Kernels keep hi in scalar registers: the host cuts a
+// call where the index passes a multiple of 2^32 (index_end), and the batch
+// kernel a tile, so one loop's elements share it.
+struct Index {
+    uint32_t lo, hi;
+    __device__ __forceinline__ Index(uint32_t l, uint32_t h) : lo(l), hi(h) {}
+    // Element e of a launch whose first index is base: the launch stays below
+    // the next multiple of 2^32.
+    static __device__ __forceinline__ Index of(uint64_t base, uint64_t e) {
+        return Index((uint32_t)base + (uint32_t)e, (uint32_t)(base >> 32));
+    }
+};
+
+// The first element at or after `begin` of a call's n elements whose global
+// index starts a new multiple of 2^32, or n.
+__host__ __device__ inline uint64_t index_end(uint64_t elem_base, uint64_t begin, uint64_t n) {
+    const uint64_t left = (1ull << 32) - (uint32_t)(elem_base + begin);
+    return n - begin < left ? n : begin + left;
+}
+
 // Blocks of one stream at one element index g.  The counters of all its
 // blocks, (lo g, hi16(g) | tag << 16 | b << 24, nonce), differ only in word 1,
-// which round 0 folds into word 0 alone.  So hi/lo(M0 lo g) of round 0,
-// M1 c2 of round 1 and M0 c0 of round 2 are the same for every block; they
-// are computed once here, and each block runs 16 multiplies instead of 20.
-// The shared words that meet a round key in rounds 1-3 are stored already
-// XORed with it, so those XORs take two VGPR operands (a full-rate VOP2)
-// instead of three.
+// which round 0 folds into word 0 alone, and only lo g differs between
+// lanes.  So in rounds 0 and 1 everything but hi/lo(M0 lo g) and M1 times the
+// round-0 word 2 is uniform (scalar unit), and those, with M0 c0 of round 2,
+// are the same for every block of the element: they are computed once here,
+// and each block runs 15 multiplies instead of 20.  The shared words that meet
+// a round key in rounds 1-3 are stored already XORed with it.
 struct StreamAt {
     uint32_t k0, k1;    // key
-    uint32_t u0;        // hi(M1 n0) ^ k0 ^ hi16(g): round-0 word 0 without the block's tag and number
+    uint32_t u0;        // hi(M1 n0) ^ k0 ^ hi16(g): round-0 word 0 without the block's tag and number (uniform)
     uint32_t c3k;       // round-0 output word 3 ^ round-1 key 1
     uint32_t c1k;       // round-1 output word 1 ^ round-2 key 0
     uint32_t h2k;       // hi(M0 c0) of round 2 ^ round-2 key 1
@@ -119,8 +139,8 @@ struct StreamAt {
     __device__ __forceinline__ Words4 block(uint32_t tag, uint32_t b) const {
         uint32_t a = k0, c = k1;
         launder_key(a, c);
-        const uint32_t x0 = u0 ^ ((tag << 16) | (b << 24));                      // round 0, word 0
-        const uint64_t p0 = (uint64_t)PHILOX_M0 * x0;                          // round 1
+        const uint32_t x0 = u0 ^ ((tag << 16) | (b << 24));                      // round 0, word 0: uniform
+        const uint64_t p0 = (uint64_t)PHILOX_M0 * x0;                          // round 1: uniform
         const uint32_t y2 = (uint32_t)(p0 >> 32) ^ c3k;
         const uint32_t y3 = (uint32_t)p0;
         const uint64_t p1 = (uint64_t)PHILOX_M1 * y2;                          // round 2
@@ -144,11 +164,13 @@ struct Stream {
         launder_key(a, c);
         return philox4x32_10((uint32_t)g, c1, n0, n1, a, c);
     }
+    // One block of an index with uniform high word (same words).
+    __device__ __forceinline__ Words4 block(Index g, uint32_t tag, uint32_t b) const { return at(g).block(tag, b); }
     // The shared rounds of every block at element g (same words as block()).
-    __device__ __forceinline__ StreamAt at(uint64_t g) const {
+    __device__ __forceinline__ StreamAt at(Index g) const {
         uint32_t a = k0, c = k1;
         launder_key(a, c);
-        const uint64_t P0 = (uint64_t)PHILOX_M0 * (uint32_t)g;                // round 0
+        const uint64_t P0 = (uint64_t)PHILOX_M0 * g.lo;                       // round 0
         const uint64_t P1 = (uint64_t)PHILOX_M1 * n0;
         const uint32_t e2 = (uint32_t)(P0 >> 32) ^ (n1 ^ c);
         const uint64_t Q1 = (uint64_t)PHILOX_M1 * e2;                         // round 1
@@ -156,12 +178,13 @@ struct Stream {
         const uint64_t Q2 = (uint64_t)PHILOX_M0 * c0b;                        // round 2
         return StreamAt{k0,
                         k1,
-                        (uint32_t)(P1 >> 32) ^ a ^ ((uint32_t)(g >> 32) & 0xFFFFu),
+                        (uint32_t)(P1 >> 32) ^ a ^ (g.hi & 0xFFFFu),
                         (uint32_t)P0 ^ (c + PHILOX_W1),
                         (uint32_t)Q1 ^ (a + 2u * PHILOX_W0),
                         (uint32_t)(Q2 >> 32) ^ (c + 2u * PHILOX_W1),
                         (uint32_t)Q2 ^ (c + 3u * PHILOX_W1)};
     }
+    __device__ __forceinline__ StreamAt at(uint64_t g) const { return at(Index((uint32_t)g, (uint32_t)(g >> 32))); }
 };
 
 __device__ __forceinline__ uint64_t join64(uint32_t lo, uint32_t hi) {

@@ -199,7 +199,8 @@ struct SlotTest {
             const uint32_t r0 = (uint32_t)r, r1 = 0u - (uint32_t)(r >> 32);
             const uint64_t c2 = (r + z) << 1;
             const uint64_t U = message2(v0, r0, r1, c2) - message2(v1, r0, r1, c2);
-            const int32_t k = (int32_t)((uint32_t)U * f.pinv32() << 24) >> 24;
+            int32_t k = (int32_t)((uint32_t)U * f.pinv32() << 24) >> 24;
+            asm("" : "+v"(k));       // a plain 32-bit factor: one v_mad_i64_i32
             const uint64_t e = (uint64_t)((int64_t)k * 9 + (int64_t)U);
             return (uint32_t)e | ((uint32_t)(e >> 32) ^ (uint32_t)(2 * k));
         } else {
@@ -334,7 +335,7 @@ __device__ __forceinline__ void drelu_finish(T dp, T rho, uint32_t t, T mask, T&
 // seed_02 (blocks 0 and 1 of TAG_BEAVER), [a]_1, [b]_1 from seed_12 (block 0);
 // P2 forms [c]_1 = (a0 + a1)(b0 + b1) - c0 from them.
 template <typename T>
-__device__ __forceinline__ void beaver_shares(const Stream& s02, const Stream& s12, uint64_t g, T mask, T& ba0, T& bb0,
+__device__ __forceinline__ void beaver_shares(const Stream& s02, const Stream& s12, Index g, T mask, T& ba0, T& bb0,
                                               T& bc0, T& ba1, T& bb1) {
     const StreamAt r02 = s02.at(g);
     const Words4 w0 = r02.block(TAG_BEAVER, 0);
@@ -700,7 +701,7 @@ __device__ __forceinline__ void plain_draws(const F& f, typename F::T& r, typena
 // round-1 messages go to cap[e * N + slot] (P0) and cap[(ncap + e) * N +
 // slot] (P1).
 template <typename T, int N, typename F, bool CAP>
-__device__ __forceinline__ T drelu_round1(T in0, T n1, uint64_t g, T mask, uint32_t k_lo, const Stream& s01,
+__device__ __forceinline__ T drelu_round1(T in0, T n1, Index g, T mask, uint32_t k_lo, const Stream& s01,
                                           typename F::T* cap, uint64_t ncap, uint64_t e, const F& f,
                                           uint32_t& t_out) {
     using FT = typename F::T;
@@ -762,7 +763,7 @@ __device__ __forceinline__ T drelu_round1(T in0, T n1, uint64_t g, T mask, uint3
 // k_in = 0 and in_mask = mask the same expressions are the plain load.
 template <typename T, int N, typename F, bool RELU, bool CAP>
 __device__ __forceinline__ void drelu_element_of(T x0, T x1, T& y0, T& y1, typename F::T* cap, uint64_t ncap,
-                                                 uint64_t e, uint64_t g, T mask, T in_mask, uint32_t k_in,
+                                                 uint64_t e, Index g, T mask, T in_mask, uint32_t k_in,
                                                  uint32_t k_lo, const Stream& s01, const Stream& s02,
                                                  const Stream& s12, const F& f) {
     T in0, n1;
@@ -787,7 +788,7 @@ __device__ __forceinline__ void drelu_element_of(T x0, T x1, T& y0, T& y1, typen
 // drelu_element_of from X0[e], X1[e] to Y0[e], Y1[e].
 template <typename T, int N, typename F, bool RELU, bool CAP>
 __device__ __forceinline__ void drelu_element(const T* __restrict__ X0, const T* __restrict__ X1, T* Y0, T* Y1,
-                                              typename F::T* cap, uint64_t ncap, uint64_t e, uint64_t g, T mask,
+                                              typename F::T* cap, uint64_t ncap, uint64_t e, Index g, T mask,
                                               T in_mask, uint32_t k_in, uint32_t k_lo, const Stream& s01,
                                               const Stream& s02, const Stream& s12, const F& f) {
     T y0, y1;
@@ -799,8 +800,9 @@ __device__ __forceinline__ void drelu_element(const T* __restrict__ X0, const T*
 
 // Elements of one k_drelu launch: at most 2^28, so that element indices and
 // byte offsets (and an index plus the grid's stride) stay in 32 bits; the
-// host runs a larger call as launches over consecutive ranges, each with
-// its own element offset, which gives the results of one launch.
+// host runs a larger call, or one whose global index passes a multiple of
+// 2^32, as launches over consecutive ranges, each with its own element
+// offset, which gives the results of one launch.
 constexpr uint64_t kLaunchElems = 1ull << 28;
 
 // Element i of p, addressed as p plus a 32-bit byte offset (the load or
@@ -857,7 +859,8 @@ __device__ __forceinline__ void drelu_launch_loop(const DreluKArgs& A, const F& 
         const uint32_t en = e + stride;
         const T x0n = load_buf<T>(B0, en), x1n = load_buf<T>(B1, en);   // past the last: 0, no access
         T y0, y1;
-        drelu_element_of<T, N, F, RELU, CAP>(x0, x1, y0, y1, cap, A.ncap, e, A.elem_base + e, mask, (T)A.in_mask,
+        drelu_element_of<T, N, F, RELU, CAP>(x0, x1, y0, y1, cap, A.ncap, e, Index::of(A.elem_base, e), mask,
+                                             (T)A.in_mask,
                                              A.k_in, A.k_lo, A.s01, A.s02, A.s12, f);
         store_at(Y0, e, y0);
         store_at(Y1, e, y1);
@@ -899,7 +902,7 @@ __global__ BC_KERNEL_ATTRS void k_drelu(DreluKArgs A, F f_arg) {
 // messages.
 template <typename T, int N, typename F, bool RELU, int G>
 __device__ __forceinline__ void drelu_element_group(const T* __restrict__ X0, const T* __restrict__ X1, T* Y0, T* Y1,
-                                                    uint64_t e, uint64_t g, uint32_t lane, T mask, T in_mask,
+                                                    uint64_t e, Index g, uint32_t lane, T mask, T in_mask,
                                                     uint32_t k_in, uint32_t k_lo, const Stream& s01,
                                                     const Stream& s02, const Stream& s12, const F& f) {
     using FT = typename F::T;
@@ -1026,7 +1029,7 @@ __global__ BC_KERNEL_ATTRS void k_drelu_group(DreluKArgs A, F f_arg) {
     const uint64_t total = A.n * G;
     for (uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += stride) {
         const uint64_t e = t / G;
-        drelu_element_group<T, N, F, RELU, G>(X0, X1, Y0, Y1, e, A.elem_base + e, lane, mask, (T)A.in_mask, A.k_in,
+        drelu_element_group<T, N, F, RELU, G>(X0, X1, Y0, Y1, e, Index::of(A.elem_base, e), lane, mask, (T)A.in_mask, A.k_in,
                                               A.k_lo, A.s01, A.s02, A.s12, f);
     }
 }
@@ -1057,35 +1060,48 @@ inline DreluKArgs make_kargs(const DreluLaunch& L) {
     return A;
 }
 
+// Calls launch(begin, end) for the consecutive ranges of n elements that share
+// the high word of their global index (one, unless it passes a multiple of
+// 2^32), and returns the first launch error.
+template <typename Fn>
+hipError_t by_index_range(uint64_t elem_base, uint64_t n, Fn&& launch) {
+    for (uint64_t begin = 0, end; begin < n; begin = end) {
+        end = index_end(elem_base, begin, n);
+        launch(begin, end);
+        const hipError_t err = hipGetLastError();
+        if (err != hipSuccess) return err;
+    }
+    return hipSuccess;
+}
+
 template <typename T, int N, typename F, bool RELU>
 hipError_t launch_field(const DreluLaunch& L, const F& f, hipStream_t st) {
     const DreluKArgs A = make_kargs(L);
-    if (L.group == 8)
-        hipLaunchKernelGGL((k_drelu_group<T, N, F, RELU, 8>), dim3(L.grid), dim3(L.block), 0, st, A, f);
-    else if (L.group == 4)
-        hipLaunchKernelGGL((k_drelu_group<T, N, F, RELU, 4>), dim3(L.grid), dim3(L.block), 0, st, A, f);
-    else {
-        // consecutive ranges of at most kLaunchElems elements
-        for (uint64_t off = 0; off < L.n; off += kLaunchElems) {
-            DreluKArgs R = A;
-            R.n = L.n - off < kLaunchElems ? L.n - off : kLaunchElems;
-            R.x0 = static_cast<const T*>(A.x0) + off;
-            R.x1 = static_cast<const T*>(A.x1) + off;
-            R.y0 = static_cast<T*>(A.y0) + off;
-            R.y1 = static_cast<T*>(A.y1) + off;
-            R.elem_base = A.elem_base + off;
-            if (L.cap) {
-                R.cap = static_cast<typename F::T*>(A.cap) + off * N;
-                hipLaunchKernelGGL((k_drelu<T, N, F, RELU, true>), dim3(L.grid), dim3(L.block), 0, st, R, f);
-            } else {
-                hipLaunchKernelGGL((k_drelu<T, N, F, RELU, false>), dim3(L.grid), dim3(L.block), 0, st, R, f);
-            }
-            const hipError_t err = hipGetLastError();
-            if (err != hipSuccess) return err;
-        }
-        return hipSuccess;
+    // consecutive ranges of at most kLaunchElems elements that share the high
+    // word of their global index
+    for (uint64_t off = 0, end; off < L.n; off = end) {
+        end = index_end(L.elem_base, off, L.n);
+        if (end - off > kLaunchElems) end = off + kLaunchElems;
+        DreluKArgs R = A;
+        R.n = end - off;
+        R.x0 = static_cast<const T*>(A.x0) + off;
+        R.x1 = static_cast<const T*>(A.x1) + off;
+        R.y0 = static_cast<T*>(A.y0) + off;
+        R.y1 = static_cast<T*>(A.y1) + off;
+        R.elem_base = A.elem_base + off;
+        if (L.cap) R.cap = static_cast<typename F::T*>(A.cap) + off * N;
+        if (L.group == 8)
+            hipLaunchKernelGGL((k_drelu_group<T, N, F, RELU, 8>), dim3(L.grid), dim3(L.block), 0, st, R, f);
+        else if (L.group == 4)
+            hipLaunchKernelGGL((k_drelu_group<T, N, F, RELU, 4>), dim3(L.grid), dim3(L.block), 0, st, R, f);
+        else if (L.cap)
+            hipLaunchKernelGGL((k_drelu<T, N, F, RELU, true>), dim3(L.grid), dim3(L.block), 0, st, R, f);
+        else
+            hipLaunchKernelGGL((k_drelu<T, N, F, RELU, false>), dim3(L.grid), dim3(L.block), 0, st, R, f);
+        const hipError_t err = hipGetLastError();
+        if (err != hipSuccess) return err;
     }
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 constexpr bool mersenne_exponent(int k) { return k == 13 || k == 17 || k == 19; }   // 2^k - 1 prime, 12 < k <= 24

@@ -37,7 +37,7 @@ struct PreKArgs {
     const uint32_t* perm;
     const void* rz;
     const void* tail;
-    uint64_t n;
+    uint64_t n, begin, end;   // this launch: elements [begin, end) of the call's n
     uint64_t elem_base;
     uint64_t ring_mask;
     uint32_t k_lo, pad;
@@ -48,7 +48,7 @@ struct ExpandKArgs {
     uint32_t* perm;
     void* rz;
     void* tail;
-    uint64_t n;
+    uint64_t n, begin, end;   // as in PreKArgs
     uint64_t elem_base;
     uint64_t ring_mask;
     Stream s01, s02, s12;
@@ -67,8 +67,8 @@ __global__ BC_KERNEL_ATTRS void k_expand(ExpandKArgs A, F f) {
     const T mask = (T)A.ring_mask;
     const uint64_t n = A.n;
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += stride) {
-        const uint64_t g = A.elem_base + e;
+    for (uint64_t e = A.begin + (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < A.end; e += stride) {
+        const Index g = Index::of(A.elem_base + A.begin, e - A.begin);
         const StreamAt r01 = A.s01.at(g);
         uint32_t perm[(N + 3) / 4];
         const uint32_t t = shuffle_perm<N>(r01, perm);
@@ -125,7 +125,7 @@ __device__ __forceinline__ RecordView<T> record_view(const void* rand, uint32_t 
 // to cap[e * N + slot] and cap[(R.n + e) * N + slot].
 template <typename T, int N, typename F, bool RELU, bool CAP>
 __device__ __forceinline__ void drelu_pre_element(const T* __restrict__ X0, const T* __restrict__ X1, T* Y0, T* Y1,
-                                                  typename F::T* cap, const RecordView<T>& R, uint64_t e, uint64_t g,
+                                                  typename F::T* cap, const RecordView<T>& R, uint64_t e, Index g,
                                                   T mask, T in_mask, uint32_t k_in, uint32_t k_lo, const Stream& s02,
                                                   const Stream& s12, const F& f) {
     using FT = typename F::T;
@@ -192,8 +192,8 @@ __device__ __forceinline__ void drelu_pre_loop(const PreKArgs& A, const F& f, T 
     typename F::T* cap = static_cast<typename F::T*>(A.cap);
     const RecordView<T> R{A.perm, static_cast<const uint64_t*>(A.rz), static_cast<const T*>(A.tail), A.n};
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < A.n; e += stride)
-        drelu_pre_element<T, N, F, RELU, CAP>(X0, X1, Y0, Y1, cap, R, e, A.elem_base + e, mask, mask, 0, A.k_lo,
+    for (uint64_t e = A.begin + (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < A.end; e += stride)
+        drelu_pre_element<T, N, F, RELU, CAP>(X0, X1, Y0, Y1, cap, R, e, Index::of(A.elem_base + A.begin, e - A.begin), mask, mask, 0, A.k_lo,
                                               A.s02, A.s12, f);
 }
 
@@ -227,11 +227,14 @@ hipError_t launch_pre_field(const PreLaunch& L, const F& f, hipStream_t st) {
         A.s01 = Stream{L.s01.k0, L.s01.k1, L.s01.n0, L.s01.n1};
         A.s02 = Stream{L.s02.k0, L.s02.k1, L.s02.n0, L.s02.n1};
         A.s12 = Stream{L.s12.k0, L.s12.k1, L.s12.n0, L.s12.n1};
-        if (L.relu)
-            hipLaunchKernelGGL((k_expand<T, N, F, true>), dim3(L.grid), dim3(256), 0, st, A, f);
-        else
-            hipLaunchKernelGGL((k_expand<T, N, F, false>), dim3(L.grid), dim3(256), 0, st, A, f);
-        return hipGetLastError();
+        return by_index_range(L.elem_base, L.n, [&](uint64_t begin, uint64_t end) {
+            A.begin = begin;
+            A.end = end;
+            if (L.relu)
+                hipLaunchKernelGGL((k_expand<T, N, F, true>), dim3(L.grid), dim3(256), 0, st, A, f);
+            else
+                hipLaunchKernelGGL((k_expand<T, N, F, false>), dim3(L.grid), dim3(256), 0, st, A, f);
+        });
     }
     PreKArgs A;
     A.x0 = L.x0;
@@ -249,14 +252,17 @@ hipError_t launch_pre_field(const PreLaunch& L, const F& f, hipStream_t st) {
     A.pad = 0;
     A.s02 = Stream{L.s02.k0, L.s02.k1, L.s02.n0, L.s02.n1};
     A.s12 = Stream{L.s12.k0, L.s12.k1, L.s12.n0, L.s12.n1};
-    if (L.relu) {
-        if (L.cap) hipLaunchKernelGGL((k_drelu_pre<T, N, F, true, true>), dim3(L.grid), dim3(256), 0, st, A, f);
-        else hipLaunchKernelGGL((k_drelu_pre<T, N, F, true, false>), dim3(L.grid), dim3(256), 0, st, A, f);
-    } else {
-        if (L.cap) hipLaunchKernelGGL((k_drelu_pre<T, N, F, false, true>), dim3(L.grid), dim3(256), 0, st, A, f);
-        else hipLaunchKernelGGL((k_drelu_pre<T, N, F, false, false>), dim3(L.grid), dim3(256), 0, st, A, f);
-    }
-    return hipGetLastError();
+    return by_index_range(L.elem_base, L.n, [&](uint64_t begin, uint64_t end) {
+        A.begin = begin;
+        A.end = end;
+        if (L.relu) {
+            if (L.cap) hipLaunchKernelGGL((k_drelu_pre<T, N, F, true, true>), dim3(L.grid), dim3(256), 0, st, A, f);
+            else hipLaunchKernelGGL((k_drelu_pre<T, N, F, true, false>), dim3(L.grid), dim3(256), 0, st, A, f);
+        } else {
+            if (L.cap) hipLaunchKernelGGL((k_drelu_pre<T, N, F, false, true>), dim3(L.grid), dim3(256), 0, st, A, f);
+            else hipLaunchKernelGGL((k_drelu_pre<T, N, F, false, false>), dim3(L.grid), dim3(256), 0, st, A, f);
+        }
+    });
 }
 
 template <typename T, int N>

@@ -41,7 +41,7 @@ struct RssKArgs {
     void* y1;
     void* y2;
     void* cap;
-    uint64_t n;
+    uint64_t n, begin, end;   // this launch: elements [begin, end) of the call's n
     uint64_t elem_base;
     uint64_t ring_mask;
     uint32_t k_lo;
@@ -66,7 +66,7 @@ __device__ __forceinline__ T word_pair(uint32_t lo, uint32_t hi) {
 template <typename T, int N, typename F, bool RELU, bool CAP>
 __device__ __forceinline__ void rss_element(const RssKArgs& A, const T* __restrict__ X0, const T* __restrict__ X1,
                                             const T* __restrict__ X2, T* Y0, T* Y1, T* Y2,
-                                            typename F::T* cap, uint64_t e, uint64_t g, T mask, const F& f) {
+                                            typename F::T* cap, uint64_t e, Index g, T mask, const F& f) {
     const T x[3] = {ld_nt(&X0[e]), ld_nt(&X1[e]), ld_nt(&X2[e])};
 
     // round 1 and P2's zero test on the 2-of-2 input ([x]_0 + [x]_1, [x]_2),
@@ -129,8 +129,8 @@ __device__ __forceinline__ void rss_loop(const RssKArgs& A, const F& f, T mask) 
     T* Y2 = static_cast<T*>(A.y2);
     typename F::T* cap = static_cast<typename F::T*>(A.cap);
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < A.n; e += stride)
-        rss_element<T, N, F, RELU, CAP>(A, X0, X1, X2, Y0, Y1, Y2, cap, e, A.elem_base + e, mask, f);
+    for (uint64_t e = A.begin + (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < A.end; e += stride)
+        rss_element<T, N, F, RELU, CAP>(A, X0, X1, X2, Y0, Y1, Y2, cap, e, Index::of(A.elem_base + A.begin, e - A.begin), mask, f);
 }
 
 // On a full-width ring the loop runs with the ring mask as a constant (see
@@ -169,11 +169,14 @@ hipError_t launch_rss_exact(const RssLaunch& L, hipStream_t st) {
     A.s2 = stream_of(L.s2);
     return with_field<N>(L.p, [&](auto f) {
         using F = decltype(f);
-        if (L.cap)
-            hipLaunchKernelGGL((k_rss<T, N, F, RELU, true>), dim3(L.grid), dim3(256), 0, st, A, f);
-        else
-            hipLaunchKernelGGL((k_rss<T, N, F, RELU, false>), dim3(L.grid), dim3(256), 0, st, A, f);
-        return hipGetLastError();
+        return by_index_range(L.elem_base, L.n, [&](uint64_t begin, uint64_t end) {
+            A.begin = begin;
+            A.end = end;
+            if (L.cap)
+                hipLaunchKernelGGL((k_rss<T, N, F, RELU, true>), dim3(L.grid), dim3(256), 0, st, A, f);
+            else
+                hipLaunchKernelGGL((k_rss<T, N, F, RELU, false>), dim3(L.grid), dim3(256), 0, st, A, f);
+        });
     });
 }
 

@@ -23,7 +23,8 @@ struct SplitKArgs {
     const void* in1;      // reply: P1's message
     void* out0;           // send: the message; reply: P0's reply share; finish: the output share
     void* out1;           // reply: P1's reply share
-    uint64_t n, elem_base, ring_mask;
+    uint64_t n, begin, end;   // this launch: elements [begin, end) of the call's n
+    uint64_t elem_base, ring_mask;
     uint32_t k_lo;
     Stream s01, s02;
 };
@@ -74,8 +75,8 @@ __global__ BC_KERNEL_ATTRS void k_send(SplitKArgs A, F f_arg) {
     uint32_t* M = static_cast<uint32_t*>(A.out0);
     const T mask = in_vgpr((T)A.ring_mask);
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < A.n; e += stride) {
-        const uint64_t g = A.elem_base + e;
+    for (uint64_t e = A.begin + (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < A.end; e += stride) {
+        const Index g = Index::of(A.elem_base + A.begin, e - A.begin);
         const T x = X[e] & mask;
         const StreamAt r01 = A.s01.at(g);
         ShuffleDigits<N> digits(r01);
@@ -109,7 +110,7 @@ __global__ BC_KERNEL_ATTRS void k_reply(SplitKArgs A, F f_arg) {
     T* D1 = static_cast<T*>(A.out1);
     const T mask = in_vgpr((T)A.ring_mask);
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < A.n; e += stride) {
+    for (uint64_t e = A.begin + (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < A.end; e += stride) {
         uint32_t w0[W], w1[W];
 #pragma unroll
         for (int k = 0; k < W; ++k) {
@@ -123,7 +124,7 @@ __global__ BC_KERNEL_ATTRS void k_reply(SplitKArgs A, F f_arg) {
             least = v < least ? v : least;
         }
         const T dp = least == 0 ? 1 : 0;                              // D'
-        const Words4 w = A.s02.block(A.elem_base + e, TAG_RESP, 0);    // rho from seed_02
+        const Words4 w = A.s02.block(Index::of(A.elem_base + A.begin, e - A.begin), TAG_RESP, 0);    // rho from seed_02
         const T rho = (T)join64(w.w0, w.w1) & mask;
         st_nt(&D0[e], rho);
         st_nt(&D1[e], (T)((T)(dp - rho) & mask));
@@ -136,9 +137,9 @@ __global__ __launch_bounds__(256) void k_finish(SplitKArgs A) {
     T* Y = static_cast<T*>(A.out0);
     const T mask = (T)A.ring_mask;
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < A.n; e += stride) {
+    for (uint64_t e = A.begin + (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < A.end; e += stride) {
         // t is the shuffle's first digit (radix 2) of chunk 0: the top bit of its high word
-        const uint32_t t = A.s01.block(A.elem_base + e, TAG_SHUFFLE, 0).w1 >> 31;
+        const uint32_t t = A.s01.block(Index::of(A.elem_base + A.begin, e - A.begin), TAG_SHUFFLE, 0).w1 >> 31;
         const T d = D[e] & mask;
         if constexpr (PARTY == 0)
             Y[e] = (T)((d ^ ((T)0 - (T)t)) + (T)(2 * t)) & mask;      // t + (1 - 2t) d
@@ -164,16 +165,19 @@ inline SplitKArgs make_split_kargs(const SplitLaunch& L) {
 
 template <typename T, int N>
 hipError_t launch_split_exact(const SplitLaunch& L, hipStream_t st) {
-    const SplitKArgs A = make_split_kargs(L);
+    SplitKArgs A = make_split_kargs(L);
     return with_field<N>(L.p, [&](auto f) {
         using F = decltype(f);
-        if (L.kind == SplitLaunch::SEND && L.party == 0)
-            hipLaunchKernelGGL((k_send<T, N, F, 0>), dim3(L.grid), dim3(256), 0, st, A, f);
-        else if (L.kind == SplitLaunch::SEND)
-            hipLaunchKernelGGL((k_send<T, N, F, 1>), dim3(L.grid), dim3(256), 0, st, A, f);
-        else
-            hipLaunchKernelGGL((k_reply<T, N, F>), dim3(L.grid), dim3(256), 0, st, A, f);
-        return hipGetLastError();
+        return by_index_range(L.elem_base, L.n, [&](uint64_t begin, uint64_t end) {
+            A.begin = begin;
+            A.end = end;
+            if (L.kind == SplitLaunch::SEND && L.party == 0)
+                hipLaunchKernelGGL((k_send<T, N, F, 0>), dim3(L.grid), dim3(256), 0, st, A, f);
+            else if (L.kind == SplitLaunch::SEND)
+                hipLaunchKernelGGL((k_send<T, N, F, 1>), dim3(L.grid), dim3(256), 0, st, A, f);
+            else
+                hipLaunchKernelGGL((k_reply<T, N, F>), dim3(L.grid), dim3(256), 0, st, A, f);
+        });
     });
 }
 

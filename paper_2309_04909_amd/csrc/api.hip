@@ -199,8 +199,9 @@ int grid_cap(int per_cu) { return bc::device_cus() * per_cu; }
 constexpr int kKinds = 7;
 std::atomic<uint32_t> g_sched[kKinds][34][2][2];
 // blocks per CU of each kind; for BC_SCHED_GROUP the largest lanes per element,
-// for BC_SCHED_GROUP_FILL the waves per SIMD lane groups may fill
-constexpr uint32_t kDefaultBpc[kKinds] = {16, 8, 16, 16, 8, 8, 1};
+// for BC_SCHED_GROUP_FILL the waves per SIMD that calls with more than one
+// lane per element may fill
+constexpr uint32_t kDefaultBpc[kKinds] = {16, 8, 16, 16, 8, 8, 2};
 
 uint32_t sched_value(uint32_t kind, uint32_t npos, uint32_t width, bool relu) {
     const uint32_t v =
@@ -208,20 +209,24 @@ uint32_t sched_value(uint32_t kind, uint32_t npos, uint32_t width, bool relu) {
     return v ? v : kDefaultBpc[kind];
 }
 
-// Lanes per element of a DReLU/ReLU call: calls too small to give every SIMD
-// `fill` waves at one lane per element (BC_SCHED_GROUP_FILL, default one)
-// spread each element over 8 or 4 lanes (up to the group schedule's limit)
-// while the grid stays within `fill` waves per SIMD; beyond that the lanes'
-// repeated shuffle costs more than the latency it hides (measured
-// on MI355X per window count; the tuner sets both limits).  Capturing calls
-// keep one lane per element.
+// Lanes per element of a DReLU/ReLU call (one lane in each of G waves, which
+// split the element's slots: k_drelu_waves).  A wave issues one VALU
+// instruction every 8.4 cycles however few waves its SIMD has, so at one lane
+// per element a call that fills no SIMD twice takes one wave's whole
+// instruction stream; G = 4 or 2 lanes shorten it while the grid stays within
+// `fill` waves per SIMD (BC_SCHED_GROUP_FILL, default 2: there the SIMD's
+// issue slots are full, and more waves only add repeated shuffles).  DReLU at
+// l_x = 32, 1 / 2 / 4 lanes: 10.2 / 7.0 / 6.6 us at 32,768 elements,
+// 10.2 / 8.5 / 9.2 at 65,536, 12.7 / 14.2 / 15.5 at 131,072; l_x = 18:
+// 5.2 / 4.1 / 3.9, 5.2 / 4.5 / 5.0 and 5.9 / 5.8 / 6.7.  Capturing calls keep
+// one lane per element.
 int lanes_per_element(uint32_t npos, uint32_t width, bool relu, uint64_t n, bool capture) {
     if (capture) return 1;
     const uint32_t gmax = sched_value(BC_SCHED_GROUP, npos, width, relu);
     const uint64_t fill = sched_value(BC_SCHED_GROUP_FILL, npos, width, relu);
     const uint64_t target = (uint64_t)bc::device_cus() * 4 * 64 * fill;   // `fill` waves on each of 4 SIMDs per CU
-    if (gmax >= 8 && n * 8 <= target) return 8;
-    if (gmax >= 4 && n * 4 <= target) return 4;
+    if (gmax >= 4 && n <= target / 4) return 4;
+    if (gmax >= 2 && n <= target / 2) return 2;
     return 1;
 }
 

@@ -471,21 +471,36 @@ struct ShuffleDigits {
     }
 };
 
-// The shuffle proper (digits j_1, ... still to come) over entries of type U,
-// entry(k) being the one of position k.
-template <int N, typename U, typename Entry>
-__device__ __forceinline__ uint8_t* shuffle_run(ShuffleDigits<N>& digits, Entry&& entry) {
+// This block's LDS array of shuffle entries: one per (N, U), whoever runs the
+// shuffle.
+template <int N, typename U>
+__device__ __forceinline__ U* shuffle_lds() {
     __shared__ U lds[N * 256];
+    return lds;
+}
+
+// The shuffle proper (digits j_1, ... still to come) over entries of type U,
+// entry(k) being the one of position k.  work(k) runs between the read and
+// the writes of swap k: independent work placed there covers the read's
+// latency where few waves share a SIMD.
+template <int N, typename U, typename Entry, typename Work>
+__device__ __forceinline__ uint8_t* shuffle_run(ShuffleDigits<N>& digits, Entry&& entry, Work&& work) {
     constexpr int ROW = 256 * (int)sizeof(U);
-    uint8_t* A = reinterpret_cast<uint8_t*>(lds + threadIdx.x);
+    uint8_t* A = reinterpret_cast<uint8_t*>(shuffle_lds<N, U>() + threadIdx.x);
     *reinterpret_cast<U*>(A) = entry(0);                      // A[0] = 0
 #pragma unroll
     for (int k = 1; k < N; ++k) {
         U* aj = reinterpret_cast<U*>(A + digits.digit(k) * ROW);
-        *reinterpret_cast<U*>(A + k * ROW) = *aj;             // A[k] = A[j_k]
+        const U old = *aj;
+        work(k);
+        *reinterpret_cast<U*>(A + k * ROW) = old;             // A[k] = A[j_k]
         *aj = entry(k);                                       // A[j_k] = k
     }
     return A;
+}
+template <int N, typename U, typename Entry>
+__device__ __forceinline__ uint8_t* shuffle_run(ShuffleDigits<N>& digits, Entry&& entry) {
+    return shuffle_run<N, U>(digits, entry, [](int) {});
 }
 
 // A filled slice of window positions.  The factors are read through a
@@ -507,11 +522,15 @@ struct ShuffledPositions {
 };
 
 // The shuffle of the window positions, after t was taken from the digits.
-template <int N>
-__device__ __forceinline__ ShuffledPositions<N> shuffle_fill(ShuffleDigits<N>& digits) {
+template <int N, typename Work>
+__device__ __forceinline__ ShuffledPositions<N> shuffle_fill(ShuffleDigits<N>& digits, Work&& work) {
     using S = ShuffleSlice<N>;
     using U = typename S::U;
-    return ShuffledPositions<N>(shuffle_run<N, U>(digits, [](int k) { return S::entry(k); }));
+    return ShuffledPositions<N>(shuffle_run<N, U>(digits, [](int k) { return S::entry(k); }, work));
+}
+template <int N>
+__device__ __forceinline__ ShuffledPositions<N> shuffle_fill(ShuffleDigits<N>& digits) {
+    return shuffle_fill<N>(digits, [](int) {});
 }
 
 // The shuffle as words: byte q of perm[k] is the position of slot 4k + q
@@ -621,10 +640,11 @@ struct MaskReader {
     }
     // The raw field of value v (shifted left by SH; with SH > 0 the low SH
     // bits are left as they come, see stream_draws).
-    __device__ __forceinline__ FT field(const StreamAt& r01, int v) {
+    __device__ __forceinline__ FT field(const StreamAt& r01, int v, bool first) {
         const int o = N * v;
         const int b = (o + N - 1) / 128;                    // the block of the field's last bit
-        if (o == 0 || (o - 1) / 128 != b) {                 // the previous field ended in an earlier block
+        if (first && o / 128 != b) cur = r01.block(TAG_MASK, (uint32_t)b - 1);   // a field that straddles two blocks
+        if (first || o == 0 || (o - 1) / 128 != b) {        // the previous field ended in an earlier block
             prev = cur.w3;
             cur = r01.block(TAG_MASK, (uint32_t)b);
         }
@@ -644,14 +664,15 @@ struct MaskReader {
             return __builtin_amdgcn_alignbit(word(k + 1, b), word(k, b), s) & M;
         }
     }
-    __device__ __forceinline__ void slot(const StreamAt& r01, int j, const F& f, FT& r, FT& z) {
+    // Slot j's draws; `first` for the first slot read when that is not slot 0.
+    __device__ __forceinline__ void slot(const StreamAt& r01, int j, const F& f, FT& r, FT& z, bool first = false) {
         if constexpr (D::STREAM) {
-            const FT R = field(r01, 2 * j);
-            const FT Z = field(r01, 2 * j + 1);
+            const FT R = field(r01, 2 * j, first);
+            const FT Z = field(r01, 2 * j + 1, false);
             stream_draws<N, F>(R, Z, r, z);
         } else {
             constexpr int SPB = D::SPB;
-            if (j % SPB == 0) cur = r01.block(TAG_MASK, (uint32_t)(j / SPB));
+            if (first || j % SPB == 0) cur = r01.block(TAG_MASK, (uint32_t)(j / SPB));
             if (j % SPB == 0)
                 block_draws<N, F, 0>(cur, f, r, z);
             else
@@ -659,27 +680,6 @@ struct MaskReader {
         }
     }
 };
-
-// The raw field of value v (STREAM) from a group's words in LDS: W[-1] and
-// W[4 NB] are zero, so every read stays inside the array.
-template <int N, typename F>
-__device__ __forceinline__ typename F::T stream_field_at(const uint32_t* W, uint32_t v) {
-    using D = MaskDraws<N, F>;
-    const int o = N * (int)v;
-    if constexpr (D::SH > 0) {
-        const int lo = o + N - 32;                  // > -32
-        const int k = ((lo + 32) >> 5) - 1;         // floor(lo / 32): -1 for v = 0
-        return __builtin_amdgcn_alignbit(W[k + 1], W[k], (uint32_t)lo & 31u);   // low SH bits as they come
-    } else if constexpr (D::WIDE) {
-        const int k = o >> 5;
-        const uint32_t s = (uint32_t)o & 31u;
-        return join64(__builtin_amdgcn_alignbit(W[k + 1], W[k], s), (W[k + 1] >> s) & 1u);
-    } else {
-        const int k = o >> 5;
-        constexpr uint32_t M = N >= 32 ? ~0u : (1u << N) - 1;
-        return __builtin_amdgcn_alignbit(W[k + 1], W[k], (uint32_t)o & 31u) & M;
-    }
-}
 
 // Plain canonical values of kept draws (captured messages, the record of the
 // precomputed mode).
@@ -891,146 +891,144 @@ __global__ BC_KERNEL_ATTRS void k_drelu(DreluKArgs A, F f_arg) {
     drelu_launch_loop<T, N, F, RELU, CAP>(A, f, in_vgpr((T)A.ring_mask));
 }
 
-// Lane groups for small calls: G consecutive lanes share one element, so a
-// call of n elements still runs n * G threads.  Every lane of the group runs
-// the whole shuffle in its own LDS slice.  Without STREAM lane l takes mask
-// block kG + l in round k and its slots (two, or one when l_x = 32); with
-// STREAM the lanes draw the blocks the same way into the group's words in
-// LDS and lane l then takes slots kG + l, reading its fields from there.
-// The group's P2 minimum is combined by lane shuffles; lane 0 finishes and
-// writes.  Results are those of drelu_element: same draws, same slots, same
-// messages.
-template <typename T, int N, typename F, bool RELU, int G>
-__device__ __forceinline__ void drelu_element_group(const T* __restrict__ X0, const T* __restrict__ X1, T* Y0, T* Y1,
-                                                    uint64_t e, Index g, uint32_t lane, T mask, T in_mask,
-                                                    uint32_t k_in, uint32_t k_lo, const Stream& s01,
-                                                    const Stream& s02, const Stream& s12, const F& f) {
+// Small calls: G waves of a block share 64 elements, so a call of n elements
+// still runs n G threads.  Role r of the G takes a fixed range of slots
+// (compile-time, so its mask fields and blocks are constants as in the
+// one-wave kernel), draws the masks of those slots only, runs the whole
+// shuffle in its own LDS slices, and hands its P2 minimum to role 0 through
+// LDS; role 0 also draws the reply (DReLU) or the triple (ReLU), finishes and
+// writes, and takes fewer slots for it.  The mask draws are placed between the
+// shuffle's LDS reads and writes, whose latency nothing else covers at one or
+// two waves on a SIMD.  Results are those of drelu_element: same draws, same
+// slots, same messages.
+// Splitting the slots over waves keeps every field offset a constant, where
+// lanes of one wave with different slots read their fields from LDS at computed
+// addresses (1,650 instructions an element and lane at N = 33 with two lanes,
+// against 1,286 here): DReLU at 65,536 elements, N = 33 9.8 -> 8.5 us, N = 19
+// 5.1 -> 4.5 us with two; 16,384 elements with four 6.4 -> 5.7 and 3.9 -> 3.7.
+template <int N, bool RELU, int G>
+struct WaveSlots {
+    // VALU instructions, roughly: a slot with its share of the mask blocks;
+    // role 0's draws and finish
+    static constexpr int SLOT = N <= 16 ? 24 : N <= 32 ? 19 + N / 2 : 58;
+    static constexpr int FINISH = RELU ? 165 : 45;
+    static constexpr int first_count() {
+        const int c = ((N * SLOT + FINISH) / G - FINISH + SLOT / 2) / SLOT;
+        return c < 0 ? 0 : c;
+    }
+    // The first slot of role r (r = G: N).
+    static constexpr int begin(int r) { return r == 0 ? 0 : first_count() + (N - first_count()) * (r - 1) / (G - 1); }
+};
+
+// Role ROLE's part of the element (in0, -n1): P2's minimum over its slots, and
+// the flip bit t.
+template <typename T, int N, typename F, bool RELU, int G, int ROLE>
+__device__ __forceinline__ uint32_t wave_slots(T in0, T n1, Index g, T mask, uint32_t k_lo, const Stream& s01, const F& f,
+                                               uint32_t& t) {
     using FT = typename F::T;
-    using D = MaskDraws<N, F>;
-    constexpr int SPB = D::SPB;                             // slots per mask block without STREAM
-    constexpr int NB = D::NB;                               // mask blocks
-    constexpr int ROUNDS = (NB + G - 1) / G;
-
-    T in0, n1;
-    input_shares<T>(ld_nt(&X0[e]), ld_nt(&X1[e]), mask, in_mask, k_in, in0, n1);
-
-    using Test = SlotTest<N, F, D::SH>;
+    using W = WaveSlots<N, RELU, G>;
+    using Test = SlotTest<N, F, MaskDraws<N, F>::SH>;
+    constexpr int J0 = W::begin(ROLE), C = W::begin(ROLE + 1) - J0;
     const StreamAt r01 = s01.at(g);
     ShuffleDigits<N> digits(r01);
-    const uint32_t t = digits.digit(0);
-    const ShuffledPositions<N> A = shuffle_fill<N>(digits);
-
-    const T a0k = flip_by(in0, t, mask) >> k_lo;         // the flip, as in drelu_round1
-    const T nb1k = flip_by(n1, t, mask) >> k_lo;
-
+    t = digits.digit(0);
     uint32_t least = 0xFFFFFFFFu;
-    if constexpr (D::STREAM) {
-        // The group's 4 NB stream words, with a zero word on either side.
-        constexpr int STRIDE = 4 * NB + 2;
-        __shared__ uint32_t mw[(256 / G) * STRIDE];
-        uint32_t* W = mw + (threadIdx.x / G) * STRIDE + 1;
-        if (lane == 0) {
-            W[-1] = 0;
-            W[4 * NB] = 0;
-        }
+    if constexpr (C > 0) {
+        const T a0k = flip_by(in0, t, mask) >> k_lo, nb1k = flip_by(n1, t, mask) >> k_lo;   // as in drelu_round1
+        MaskReader<N, F> masks;
+        FT r[C], z[C];
+        int drawn = 0;
+        const auto draw_until = [&](int count) {             // compile-time counts, once unrolled
 #pragma unroll
-        for (int k = 0; k < ROUNDS; ++k) {
-            const uint32_t blk = (uint32_t)(k * G) + lane;
-            if (blk < (uint32_t)NB) {
-                const Words4 w = r01.block(TAG_MASK, blk);
-                W[4 * blk] = w.w0;
-                W[4 * blk + 1] = w.w1;
-                W[4 * blk + 2] = w.w2;
-                W[4 * blk + 3] = w.w3;
-            }
-        }
-        wave_sync();                                        // the group's words before its reads
+            for (int i = 0; i < C; ++i)
+                if (i >= drawn && i < count) masks.slot(r01, J0 + i, f, r[i], z[i], i == 0 && J0 > 0);
+            drawn = drawn > count ? drawn : count;
+        };
+        const auto work = [&](int k) { draw_until((k * C + N - 2) / (N - 1)); };
+        if constexpr (kPairs<N>) {
+            PairWindows<T, N> win(a0k, nb1k, in_vgpr(0xFFFFFFFEu));
+            const uint8_t* A = shuffle_run<N, uint32_t>(digits, [&](int k) { return win.value(k); }, work);
 #pragma unroll
-        for (int k = 0; k < (N + G - 1) / G; ++k) {
-            const uint32_t j = (uint32_t)(k * G) + lane;
-            const bool valid = j < (uint32_t)N;
-            const uint32_t js = valid ? j : 0u;             // past the last slot: any slot, not counted
-            FT r, z;
-            stream_draws<N, F>(stream_field_at<N, F>(W, 2 * js), stream_field_at<N, F>(W, 2 * js + 1), r, z);
-            uint32_t v0, v1;
-            window_sums<T, N>(a0k, nb1k, A.pos(js), A.times(js), v0, v1);
-            const uint32_t u = Test::mark(v0, v1, r, z, f);
-            least = (valid && u < least) ? u : least;
-        }
-        wave_sync();                                        // every read before the next element's words
-    } else {
+            for (int i = 0; i < C; ++i)
+                least = min(least, Test::mark_pair(*reinterpret_cast<const uint32_t*>(A + (J0 + i) * 1024), r[i], z[i], f));
+        } else {
+            const ShuffledPositions<N> A = shuffle_fill<N>(digits, work);
 #pragma unroll
-        for (int k = 0; k < ROUNDS; ++k) {
-            const uint32_t blk = (uint32_t)(k * G) + lane;  // this lane's mask block
-            const Words4 w = r01.block(TAG_MASK, blk);
-#pragma unroll
-            for (int h = 0; h < SPB; ++h) {
-                // slot j = SPB * blk + h (past the last slot: any slot, its message is not counted)
-                const bool valid = SPB * blk + h < (uint32_t)N;
-                const uint32_t js = valid ? SPB * blk + h : 0u;
-                const uint32_t pos = A.pos(js);
-                FT r, z;
-                if (h == 0)
-                    block_draws<N, F, 0>(w, f, r, z);
-                else
-                    block_draws<N, F, (SPB > 1 ? 1 : 0)>(w, f, r, z);
+            for (int i = 0; i < C; ++i) {
                 uint32_t v0, v1;
-                window_sums<T, N>(a0k, nb1k, pos, A.times(js), v0, v1);
-                const uint32_t u = Test::mark(v0, v1, r, z, f);
-                least = (valid && u < least) ? u : least;
+                window_sums<T, N>(a0k, nb1k, A.pos(J0 + i), A.times(J0 + i), v0, v1);
+                least = min(least, Test::mark(v0, v1, r[i], z[i], f));
             }
         }
     }
-#pragma unroll
-    for (int o = 1; o < G; o <<= 1) {
-        const uint32_t other = __shfl_xor(least, o, G);
-        least = other < least ? other : least;
-    }
-    const T dp = least <= Test::LIMIT ? 1 : 0;
+    return least;
+}
 
-    T y0, y1;
-    if constexpr (!RELU) {
-        const Words4 w = s02.block(g, TAG_RESP, 0);
-        drelu_finish<T>(dp, (T)join64(w.w0, w.w1), t, mask, y0, y1);
+template <typename T, int N, typename F, bool RELU, int G, int ROLE>
+__device__ __forceinline__ uint32_t wave_role(uint32_t role, T in0, T n1, Index g, T mask, uint32_t k_lo, const Stream& s01,
+                                              const F& f, uint32_t& t) {
+    if constexpr (ROLE == G - 1) {
+        return wave_slots<T, N, F, RELU, G, ROLE>(in0, n1, g, mask, k_lo, s01, f, t);
     } else {
-        const T in1 = (T)((T)0 - n1) & mask;
-        const StreamAt r02 = s02.at(g);
-        const Words4 w0 = r02.block(TAG_BEAVER, 0);
-        const Words4 w1 = r02.block(TAG_BEAVER, 1);
-        const Words4 w2 = s12.block(g, TAG_BEAVER, 0);
-        const T ba0 = (T)join64(w0.w0, w0.w1) & mask;
-        const T bb0 = (T)join64(w0.w2, w0.w3) & mask;
-        const T bc0 = (T)join64(w1.w0, w1.w1) & mask;
-        const T ba1 = (T)join64(w2.w0, w2.w1) & mask;
-        const T bb1 = (T)join64(w2.w2, w2.w3) & mask;
-        const T bc1 = (T)((T)(ba0 + ba1) * (T)(bb0 + bb1) - bc0) & mask;
-        relu_finish<T>(dp, in0, in1, ba0, bb0, bc0, ba1, bb1, bc1, t, mask, y0, y1);
-    }
-    if (lane == 0) {
-        st_nt(&Y0[e], y0);
-        st_nt(&Y1[e], y1);
+        if (role == ROLE) return wave_slots<T, N, F, RELU, G, ROLE>(in0, n1, g, mask, k_lo, s01, f, t);
+        return wave_role<T, N, F, RELU, G, ROLE + 1>(role, in0, n1, g, mask, k_lo, s01, f, t);
     }
 }
 
-// Lane-group launch: thread t serves element t / G as lane t % G.  Every lane
-// of a group is active or inactive together (the loop bound is per element),
-// so the shuffles only read lanes that take part.
+// Blocks of 256 threads take 256 / G elements at a time: wave w serves
+// elements 64 (w / G) .. + 63 of them in role w % G.  The loop bound is the
+// block's, so every wave reaches both barriers the same number of times; a
+// lane past the last element works on that element and writes nothing.
 template <typename T, int N, typename F, bool RELU, int G>
-__global__ BC_KERNEL_ATTRS void k_drelu_group(DreluKArgs A, F f_arg) {
-    static_assert(G >= 2 && (G & (G - 1)) == 0 && 256 % G == 0, "G: a power of two dividing the block");
+__global__ BC_KERNEL_ATTRS void k_drelu_waves(DreluKArgs A, F f_arg) {
+    static_assert(G == 2 || G == 4, "G: waves of a 256-thread block that share elements");
+    constexpr uint32_t EPB = 256 / G;
+    __shared__ uint32_t least_of[256];
     const F f = f_arg.vgpr();
     const T* X0 = static_cast<const T*>(A.x0);
     const T* X1 = static_cast<const T*>(A.x1);
     T* Y0 = static_cast<T*>(A.y0);
     T* Y1 = static_cast<T*>(A.y1);
     const T mask = in_vgpr((T)A.ring_mask);
-    const uint32_t lane = threadIdx.x & (G - 1);
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    const uint64_t total = A.n * G;
-    for (uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += stride) {
-        const uint64_t e = t / G;
-        drelu_element_group<T, N, F, RELU, G>(X0, X1, Y0, Y1, e, Index::of(A.elem_base, e), lane, mask, (T)A.in_mask, A.k_in,
-                                              A.k_lo, A.s01, A.s02, A.s12, f);
+    const uint32_t n = (uint32_t)A.n;                        // at most kLaunchElems
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), role = wave % G;
+    for (uint32_t b = blockIdx.x * EPB; b < n; b += gridDim.x * EPB) {
+        const uint32_t want = b + (wave / G) * 64 + (threadIdx.x & 63u);
+        const uint32_t e = want < n ? want : n - 1;
+        const Index g = Index::of(A.elem_base, e);
+        T in0, n1;
+        input_shares<T>(load_at(X0, e), load_at(X1, e), mask, (T)A.in_mask, A.k_in, in0, n1);
+        uint32_t t;
+        uint32_t least = wave_role<T, N, F, RELU, G, 0>(role, in0, n1, g, mask, A.k_lo, A.s01, f, t);
+        if (role != 0) least_of[threadIdx.x] = least;
+        T ba0 = 0, bb0 = 0, bc0 = 0, ba1 = 0, bb1 = 0, rho = 0;
+        if (role == 0) {                                     // role 0's draws, before it waits
+            if constexpr (RELU) {
+                beaver_shares<T>(A.s02, A.s12, g, mask, ba0, bb0, bc0, ba1, bb1);
+            } else {
+                const Words4 w = A.s02.block(g, TAG_RESP, 0);
+                rho = (T)join64(w.w0, w.w1);
+            }
+        }
+        __syncthreads();
+        if (role == 0) {
+#pragma unroll
+            for (int r = 1; r < G; ++r) least = min(least, least_of[threadIdx.x + 64 * r]);
+            const T dp = least <= SlotTest<N, F, MaskDraws<N, F>::SH>::LIMIT ? 1 : 0;
+            T y0, y1;
+            if constexpr (RELU) {
+                const T in1 = (T)((T)0 - n1) & mask;
+                const T bc1 = (T)((T)(ba0 + ba1) * (T)(bb0 + bb1) - bc0) & mask;
+                relu_finish<T>(dp, in0, in1, ba0, bb0, bc0, ba1, bb1, bc1, t, mask, y0, y1);
+            } else {
+                drelu_finish<T>(dp, rho, t, mask, y0, y1);
+            }
+            if (want < n) {
+                store_at(Y0, e, y0);
+                store_at(Y1, e, y1);
+            }
+        }
+        __syncthreads();                                     // role 0 has read before the next elements' minima
     }
 }
 
@@ -1090,10 +1088,10 @@ hipError_t launch_field(const DreluLaunch& L, const F& f, hipStream_t st) {
         R.y1 = static_cast<T*>(A.y1) + off;
         R.elem_base = A.elem_base + off;
         if (L.cap) R.cap = static_cast<typename F::T*>(A.cap) + off * N;
-        if (L.group == 8)
-            hipLaunchKernelGGL((k_drelu_group<T, N, F, RELU, 8>), dim3(L.grid), dim3(L.block), 0, st, R, f);
-        else if (L.group == 4)
-            hipLaunchKernelGGL((k_drelu_group<T, N, F, RELU, 4>), dim3(L.grid), dim3(L.block), 0, st, R, f);
+        if (L.group == 4)
+            hipLaunchKernelGGL((k_drelu_waves<T, N, F, RELU, 4>), dim3(L.grid), dim3(L.block), 0, st, R, f);
+        else if (L.group == 2)
+            hipLaunchKernelGGL((k_drelu_waves<T, N, F, RELU, 2>), dim3(L.grid), dim3(L.block), 0, st, R, f);
         else if (L.cap)
             hipLaunchKernelGGL((k_drelu<T, N, F, RELU, true>), dim3(L.grid), dim3(L.block), 0, st, R, f);
         else

@@ -28,7 +28,7 @@ struct DreluLaunch {
     StreamKey s01, s02, s12;
     int grid;
     int block;
-    int group;            // lanes per element: 1, or 4 / 8 (lane-group kernel, no capture)
+    int group;            // lanes per element: 1, or 2 / 4 (k_drelu_waves, no capture)
 };
 
 // Device plan of a ragged batch: this header, then nseg bc_segment records,

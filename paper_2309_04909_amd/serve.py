@@ -101,7 +101,7 @@ class Server:
         self._arena_used = []                        # its ranges in flight: sorted (start, end) byte offsets
 
     def warmup(self):
-        """One small call per ring, op and lane-group size, so that no job pays
+        """One small call per ring, op and number of lanes per element, so that no job pays
         for loading a kernel's code object on its first launch; the output
         arena and the pinned plan buffers allocated up front, so that no launch
         waits for an allocation."""

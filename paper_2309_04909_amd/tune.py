@@ -138,7 +138,7 @@ def tune_kind(kind, settings, n, reps, ops=(B.BC_OP_DRELU, B.BC_OP_RELU)):
 
 
 def tune_group(settings, reps, sizes=(1024, 4096, 16384)):
-    """Lanes per element of small calls: the largest group (1, 4 or 8 lanes)
+    """Lanes per element of small calls: the largest number (1, 2 or 4)
     the library may use, chosen by the summed time over small call sizes."""
     out = []
     for ell, lx, k_lo in settings:
@@ -150,8 +150,8 @@ def tune_group(settings, reps, sizes=(1024, 4096, 16384)):
         for op in (B.BC_OP_DRELU, B.BC_OP_RELU):
             f = B.relu if op == B.BC_OP_RELU else B.drelu
             best, ref = None, None
-            B.set_schedule("group_fill", npos, 1, width, op)     # groups within one wave per SIMD here
-            for gmax in (1, 4, 8):
+            B.set_schedule("group_fill", npos, 1, width, op)     # one wave per SIMD here
+            for gmax in (1, 2, 4):
                 B.set_schedule("group", npos, gmax, width, op)
                 total, outs = 0.0, []
                 for (x0, x1), o in zip(calls, outs_buf):
@@ -169,10 +169,10 @@ def tune_group(settings, reps, sizes=(1024, 4096, 16384)):
 
 
 def tune_group_fill(settings, reps, sizes=(16384, 32768, 65536)):
-    """How many waves per SIMD lane groups may fill (1, 2 or 4): at the
-    larger call sizes one lane per element leaves each SIMD with one or two
-    long dependent chains, while lane groups split the slots over more waves
-    and repeat the shuffle in each.  Chosen by the summed time over sizes,
+    """How many waves per SIMD calls with several lanes per element may fill
+    (1, 2 or 4): at the larger call sizes one lane per element leaves each SIMD
+    with one or two long instruction streams, while more lanes split the slots
+    over more waves and repeat the shuffle in each.  Chosen by the summed time over sizes,
     with the group schedule already set."""
     out = []
     for ell, lx, k_lo in settings:
@@ -191,7 +191,7 @@ def tune_group_fill(settings, reps, sizes=(16384, 32768, 65536)):
                     total += _time_graph(lambda: f(x0, x1, prm, sd, out=o), reps * 2)
                     outs.append(f(x0, x1, prm, sd))
                 ref = ref or outs
-                assert all(_same(a, b) for a, b in zip(ref, outs)), "lane groups changed a result"
+                assert all(_same(a, b) for a, b in zip(ref, outs)), "lanes per element changed a result"
                 print(f"  fill   op={op} l={ell} lx={lx:2d} waves<={fill}: {total * 1e3:.1f} us", flush=True)
                 if best is None or total < best[1]:
                     best = (fill, total)

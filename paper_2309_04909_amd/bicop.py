@@ -1,11 +1,16 @@
-"""Thin ctypes binding of libbicop.so (include/bicop.h).
+"""Thin binding of libbicop.so (include/bicop.h).
 
 Argument marshalling only: every step of the protocols runs in the HIP
 kernels behind the C ABI.  Shares are torch tensors on the GPU whose element
 size matches the ring (4 bytes for l <= 32, else 8; uint32/int32 or
 uint64/int64 storage), contiguous.  Calls enqueue on the current torch
-stream unless a stream is given.  If the library is not built, importing
-this module raises ImportError: there is no fallback path.
+stream unless a stream is given.  The calls on share
+arrays (drelu, relu, their truncating and replicated forms, trunc_det,
+mul_trunc and the parties-apart calls) are marshalled by the native module
+_fastcall where their arguments are plain, and through ctypes by the code
+here otherwise: the same checks and the same C call.  If the library or the
+module is not built, importing this module raises ImportError: there is no
+fallback path.
 """
 
 import ctypes
@@ -135,6 +140,23 @@ def _load():
 
 lib = _load()
 
+try:
+    from . import _fastcall
+except ImportError as e:
+    raise ImportError(f"the _fastcall module beside {LIB_PATH} is not built; run __graft_entry__.build() "
+                      "or python -m paper_2309_04909_amd.build") from e
+
+
+def _address(fn):
+    return ctypes.cast(fn, ctypes.c_void_p).value
+
+
+_A_DRELU, _A_RELU = _address(lib.bc_drelu), _address(lib.bc_relu)
+_A_TRUNC_DRELU, _A_TRUNC_RELU = _address(lib.bc_trunc_drelu), _address(lib.bc_trunc_relu)
+_A_TRUNC_DET, _A_MUL = _address(lib.bc_trunc_det), _address(lib.bc_mul_trunc)
+_A_RSS_DRELU, _A_RSS_RELU = _address(lib.bc_rss_drelu), _address(lib.bc_rss_relu)
+_A_SEND, _A_REPLY, _A_FINISH = _address(lib.bc_drelu_send), _address(lib.bc_drelu_reply), _address(lib.bc_drelu_finish)
+
 SCHED_KINDS = {"fused": 0, "stream": 1, "pre": 2, "expand": 3, "batch": 4, "group": 5, "group_fill": 6}
 SCHED_ALL = 0xFFFFFFFF
 SCHEDULES_PATH = os.path.join(_HERE, "schedules.json")
@@ -180,6 +202,9 @@ def load_schedules(path=SCHEDULES_PATH):
 def _check(rc, where):
     if rc != 0:
         raise BicopError(rc, where, f"{lib.bc_strerror(rc).decode()}: {lib.bc_last_error().decode()}")
+
+
+_fastcall.set_check(_check)
 
 
 # ------------------------------------------------------------------ settings
@@ -327,6 +352,9 @@ def _out(x, like_width, dtype, out):
 
 def trunc_det(x0, x1, ell, k1, k2=0, out=None, stream=None):
     """Alg. 4/5: shares of Z_{2^ell} -> shares of Z_{2^(ell-k1-k2)}."""
+    y = _fastcall.cut(_A_TRUNC_DET, "trunc_det", x0, x1, ell, k1, k2, out, stream)
+    if y is not None:
+        return y
     _check_shares(x0, x1, ring_width(ell))
     m = ell - k1 - k2
     y0 = _out(x0, ring_width(m), ring_dtype(m), None if out is None else out[0])
@@ -375,11 +403,19 @@ def _drelu_like(fn, name, x0, x1, params, seeds, elem_base, capture, out, stream
 
 def drelu(x0, x1, params: Params, seeds: Seeds, elem_base=0, capture=False, out=None, stream=None):
     """Alg. 7.  Returns (y0, y1) or (y0, y1, capture[2, n, lx+1])."""
+    if not capture:
+        y = _fastcall.drelu(_A_DRELU, "drelu", x0, x1, params, seeds, elem_base, out, stream)
+        if y is not None:
+            return y
     return _drelu_like(lib.bc_drelu, "drelu", x0, x1, params, seeds, elem_base, capture, out, stream)
 
 
 def relu(x0, x1, params: Params, seeds: Seeds, elem_base=0, capture=False, out=None, stream=None):
     """Alg. 8.  Returns (y0, y1) or (y0, y1, capture[2, n, lx+1])."""
+    if not capture:
+        y = _fastcall.drelu(_A_RELU, "relu", x0, x1, params, seeds, elem_base, out, stream)
+        if y is not None:
+            return y
     return _drelu_like(lib.bc_relu, "relu", x0, x1, params, seeds, elem_base, capture, out, stream)
 
 
@@ -398,6 +434,9 @@ def _check_one(t, width, what):
 def drelu_send(party, x, params: Params, seeds: Seeds, elem_base=0, out=None, stream=None):
     """P0's (party 0) or P1's (party 1) round-1 message, from its own share x,
     bit-packed: an int32 tensor [msg_words(lx + 1), n], word-major."""
+    m = _fastcall.send(_A_SEND, "drelu_send", party, x, params, seeds, elem_base, out, stream)
+    if m is not None:
+        return m
     _check_one(x, ring_width(params.ell), "share")
     shape = (msg_words(params.npos), x.numel())
     msg = out if out is not None else torch.empty(shape, dtype=torch.int32, device=x.device)
@@ -410,6 +449,9 @@ def drelu_send(party, x, params: Params, seeds: Seeds, elem_base=0, out=None, st
 
 def drelu_reply(msg0, msg1, params: Params, seeds: Seeds, elem_base=0, out=None, stream=None):
     """P2: the zero test on both packed messages; returns its reply shares (d0, d1)."""
+    d = _fastcall.reply(_A_REPLY, "drelu_reply", msg0, msg1, params, seeds, elem_base, out, stream)
+    if d is not None:
+        return d
     n = msg0.shape[1]
     if msg0.shape != msg1.shape or msg0.shape[0] != msg_words(params.npos):
         raise ValueError("message tensors do not match the setting")
@@ -425,6 +467,9 @@ def drelu_reply(msg0, msg1, params: Params, seeds: Seeds, elem_base=0, out=None,
 
 def drelu_finish(party, d, params: Params, seeds: Seeds, elem_base=0, out=None, stream=None):
     """P0's or P1's unflip of its reply share."""
+    y = _fastcall.finish(_A_FINISH, "drelu_finish", party, d, params, seeds, elem_base, out, stream)
+    if y is not None:
+        return y
     _check_one(d, ring_width(params.ell), "reply share")
     y = _out(d, ring_width(params.ell), ring_dtype(params.ell), out)
     _check(lib.bc_drelu_finish(party, d.data_ptr(), y.data_ptr(), d.numel(), ctypes.byref(params.c()),
@@ -437,6 +482,9 @@ def mul_trunc(x0, x1, y0, y1, ell, f, order, seeds: Seeds, elem_base=0, out=None
     is Alg. linear (factors by floor(f/2) and ceil(f/2) bits first),
     BC_TRUNC_AFTER truncates the product by f, BC_TRUNC_NONE (f = 0) is the
     plain product.  Returns (z0, z1) in Z_{2^ell}."""
+    z = _fastcall.mul(_A_MUL, "mul_trunc", x0, x1, y0, y1, ell, f, order, seeds, elem_base, out, stream)
+    if z is not None:
+        return z
     w = ring_width(ell)
     _check_shares(x0, x1, w)
     _check_shares(y0, y1, w)
@@ -469,11 +517,19 @@ def _rss_like(fn, name, x, params, seeds, elem_base, capture, out, stream):
 def rss_drelu(x, params: Params, seeds: RssSeeds, elem_base=0, capture=False, out=None, stream=None):
     """Alg. drelu2 on replicated shares x = (x0, x1, x2).  Returns (y0, y1, y2),
     or ((y0, y1, y2), capture[2, n, lx+1])."""
+    if not capture:
+        y = _fastcall.rss(_A_RSS_DRELU, "rss_drelu", x, params, seeds, elem_base, out, stream)
+        if y is not None:
+            return y
     return _rss_like(lib.bc_rss_drelu, "rss_drelu", x, params, seeds, elem_base, capture, out, stream)
 
 
 def rss_relu(x, params: Params, seeds: RssSeeds, elem_base=0, capture=False, out=None, stream=None):
     """RSS ReLU (appendix) on replicated shares x = (x0, x1, x2)."""
+    if not capture:
+        y = _fastcall.rss(_A_RSS_RELU, "rss_relu", x, params, seeds, elem_base, out, stream)
+        if y is not None:
+            return y
     return _rss_like(lib.bc_rss_relu, "rss_relu", x, params, seeds, elem_base, capture, out, stream)
 
 
@@ -492,12 +548,20 @@ def _trunc_like(fn, name, x0, x1, ell_in, k1, params, seeds, elem_base, capture,
 
 def trunc_drelu(x0, x1, ell_in, k1, params: Params, seeds: Seeds, elem_base=0, capture=False, out=None, stream=None):
     """Alg. 5 by k1 bits (Z_{2^ell_in} -> Z_{2^params.ell}) fused with Alg. 7."""
+    if not capture:
+        y = _fastcall.trunc(_A_TRUNC_DRELU, "trunc_drelu", x0, x1, ell_in, k1, params, seeds, elem_base, out, stream)
+        if y is not None:
+            return y
     return _trunc_like(lib.bc_trunc_drelu, "trunc_drelu", x0, x1, ell_in, k1, params, seeds, elem_base, capture,
                        out, stream)
 
 
 def trunc_relu(x0, x1, ell_in, k1, params: Params, seeds: Seeds, elem_base=0, capture=False, out=None, stream=None):
     """Alg. 5 by k1 bits (Z_{2^ell_in} -> Z_{2^params.ell}) fused with Alg. 8."""
+    if not capture:
+        y = _fastcall.trunc(_A_TRUNC_RELU, "trunc_relu", x0, x1, ell_in, k1, params, seeds, elem_base, out, stream)
+        if y is not None:
+            return y
     return _trunc_like(lib.bc_trunc_relu, "trunc_relu", x0, x1, ell_in, k1, params, seeds, elem_base, capture,
                        out, stream)
 

@@ -1,4 +1,5 @@
-"""Build libbicop.so (the C ABI of include/bicop.h) for gfx950 with hipcc.
+"""Build libbicop.so (the C ABI of include/bicop.h) for gfx950 with hipcc, and
+the Python binding's native argument marshalling (_fastcall.so) with g++.
 
 Every .hip file under csrc/ is compiled to an object in _build/ (in parallel),
 then the objects are linked into paper_2309_04909_amd/libbicop.so.  The
@@ -28,6 +29,27 @@ FLAGS = [
     # the slot arrays are indexed dynamically, through scratch)
     "-mllvm", "-pragma-unroll-threshold=200000",
 ]
+
+
+FASTCALL = os.path.join(HERE, "_fastcall.so")
+
+
+def build_fastcall(out: str = FASTCALL) -> str:
+    """Compile csrc/fastcall.cpp, the binding's native argument marshalling (host code against torch's headers)."""
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    tmp = out + ".tmp"
+    rc, log = _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+                    "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+                    f"-I{root}/include", f"-I{root}/include/torch/csrc/api/include", "-I/opt/rocm/include",
+                    f"-I{sysconfig.get_paths()['include']}", os.path.join(CSRC, "fastcall.cpp"), "-o", tmp,
+                    f"-L{root}/lib", "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", f"-Wl,-rpath,{root}/lib"])
+    if rc != 0:
+        raise RuntimeError("the _fastcall module failed to build:\n" + log)
+    os.replace(tmp, out)
+    return out
 
 
 def sources():
@@ -69,13 +91,16 @@ def build(jobs: int | None = None, verbose: bool = False, asm: bool = False, ext
     if rc != 0:
         raise RuntimeError("link failed:\n" + log)
     os.replace(tmp, out)
+    if out == LIB:
+        build_fastcall()
     return out
 
 
 def clean():
     shutil.rmtree(BUILD, ignore_errors=True)
-    if os.path.exists(LIB):
-        os.remove(LIB)
+    for path in (LIB, FASTCALL):
+        if os.path.exists(path):
+            os.remove(path)
 
 
 if __name__ == "__main__":

@@ -175,6 +175,10 @@ struct SlotTest {
     static constexpr uint32_t K = SMALL ? (1u << (N - 1)) - 1 : 0;
     static constexpr uint32_t LIMIT = 2 * K;
 
+    uint64_t zero_high;
+    __device__ __forceinline__ SlotTest() {
+        if constexpr (!SMALL && N <= 31) asm("v_mov_b64 %0, 0" : "=v"(zero_high));
+    }
     static __device__ __forceinline__ uint32_t mark_small(uint32_t m0, uint32_t m1, const F& f) {
         return (uint32_t)mad_u64_u32(m0 - m1, f.pinv32(), K);
     }
@@ -183,12 +187,22 @@ struct SlotTest {
         const uint32_t c = r + z;
         return mark_small(mad_half<false>(pair, r, c), mad_half<true>(pair, r, c), f);
     }
-    static __device__ __forceinline__ uint32_t mark(uint32_t v0, uint32_t v1, FT r, FT z, const F& f) {
+    __device__ __forceinline__ uint32_t mark(uint32_t v0, uint32_t v1, FT r, FT z, const F& f) {
         if constexpr (SMALL) {
             const uint32_t c = r + z;
             return mark_small(mad_half<false>(v0, r, c), mad_half<false>(v1, r, c), f);
         } else if constexpr (N <= 32) {
-            const uint64_t c = add_wide(r, z);
+            uint64_t c;
+            if constexpr (N <= 31) {
+                // r + z through a register pair whose high word stays zero from
+                // slot to slot, which the compiler would set again for each
+                // (N = 19: 708 -> 691 instructions); at N = 32 z is a stream
+                // word that would have to be moved there
+                zero_high = (zero_high & 0xFFFFFFFF00000000ull) | z;
+                c = mad_u64_u32(r, 1u, zero_high);
+            } else {
+                c = add_wide(r, z);
+            }
             const uint64_t D = mad_u64_u32(v0, r, c) - mad_u64_u32(v1, r, c);
             const uint32_t k = (uint32_t)D * f.pinv32();
             if constexpr (N <= 31)
@@ -710,6 +724,7 @@ __device__ __forceinline__ T drelu_round1(T in0, T n1, Index g, T mask, uint32_t
 
     const StreamAt r01 = s01.at(g);
     using Test = SlotTest<N, F, MaskDraws<N, F>::SH>;
+    Test test;
     LeastMark<N> p2;
     MaskReader<N, F> masks;
     ShuffleDigits<N> digits(r01);
@@ -746,7 +761,7 @@ __device__ __forceinline__ T drelu_round1(T in0, T n1, Index g, T mask, uint32_t
                 const FT w = addmod(w0, w1, f);                // P2 reconstructs and tests
                 p2.take(j, w == 0 ? 0u : 0xFFFFFFFFu);
             } else {
-                p2.take(j, Test::mark(v0, v1, r, z, f));
+                p2.take(j, test.mark(v0, v1, r, z, f));
             }
         }
     }
@@ -953,11 +968,12 @@ __device__ __forceinline__ uint32_t wave_slots(T in0, T n1, Index g, T mask, uin
                 least = min(least, Test::mark_pair(*reinterpret_cast<const uint32_t*>(A + (J0 + i) * 1024), r[i], z[i], f));
         } else {
             const ShuffledPositions<N> A = shuffle_fill<N>(digits, work);
+            Test test;
 #pragma unroll
             for (int i = 0; i < C; ++i) {
                 uint32_t v0, v1;
                 window_sums<T, N>(a0k, nb1k, A.pos(J0 + i), A.times(J0 + i), v0, v1);
-                least = min(least, Test::mark(v0, v1, r[i], z[i], f));
+                least = min(least, test.mark(v0, v1, r[i], z[i], f));
             }
         }
     }

@@ -140,6 +140,7 @@ __device__ __forceinline__ void drelu_pre_element(const T* __restrict__ X0, cons
     const T nb1 = flip_by(n1, t, mask);
     const T a0k = a0 >> k_lo, nb1k = nb1 >> k_lo;
     using Test = SlotTest<N, F, 0>;
+    Test test;
     LeastMark<N> p2;
     constexpr int K = RzLayout<N>::K;
     uint64_t cur = 0;                                  // the word being read
@@ -164,7 +165,7 @@ __device__ __forceinline__ void drelu_pre_element(const T* __restrict__ X0, cons
             const FT w = addmod(w0, w1, f);
             p2.take(j, w == 0 ? 0u : 0xFFFFFFFFu);
         } else {
-            p2.take(j, Test::mark(v0, v1, r, z, f));
+            p2.take(j, test.mark(v0, v1, r, z, f));
         }
     }
     const T dp = p2.least <= Test::LIMIT ? 1 : 0;

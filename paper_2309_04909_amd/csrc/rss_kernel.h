@@ -93,14 +93,15 @@ __device__ __forceinline__ void rss_element(const RssKArgs& A, const T* __restri
     rss_product<T>(ss, ts, gst, st);
 
     // P2's public reply and the finish: y_j = q_j - 2 D'' q_j (+ D'' on share 0)
-    const T dpp = dp ^ s;
+    // (the sign as xor and add: a select per word costs what both do, and the
+    // add of D'' on share 0 is the negation's own + 1)
+    const T dpp = dp ^ s, neg = (T)((T)0 - dpp);
     T y[3];
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
         const T q = (T)(ss[j] + ts[j] - (T)2 * st[j]);               // [s xor t]_j
-        y[j] = dpp ? (T)((T)0 - q) : q;
+        y[j] = (T)((q ^ neg) + (j == 0 ? (T)(2 * dpp) : dpp));
     }
-    y[0] = (T)(y[0] + dpp);
 
     if constexpr (RELU) {
         const Words4 b4 = r012.block(TAG_RSS, 4);

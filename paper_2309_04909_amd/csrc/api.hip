@@ -200,8 +200,12 @@ constexpr int kKinds = 7;
 std::atomic<uint32_t> g_sched[kKinds][34][2][2];
 // blocks per CU of each kind; for BC_SCHED_GROUP the largest lanes per element,
 // for BC_SCHED_GROUP_FILL the waves per SIMD that calls with more than one
-// lane per element may fill
-constexpr uint32_t kDefaultBpc[kKinds] = {16, 8, 16, 16, 8, 8, 2};
+// lane per element may fill.  A compute unit holds 7 or 8 blocks of the slot
+// kernels; eight times as many let it take the next block as one ends instead
+// of waiting for the slowest walk of a persistent block.  Ragged batch of
+// 9,232,384 elements at 8 / 16 / 64: l_x = 18 209 / 198 / 197 us, l_x = 11
+// (l = 51) 167 / 158 / 155, l_x = 8 (l = 32) 134 / 124 / 121.
+constexpr uint32_t kDefaultBpc[kKinds] = {16, 8, 16, 16, 64, 8, 2};
 
 uint32_t sched_value(uint32_t kind, uint32_t npos, uint32_t width, bool relu) {
     const uint32_t v =

@@ -91,11 +91,11 @@ __device__ __forceinline__ void batch_walk(const bc_segment* __restrict__ segs,
                 const RecordView<T> R = record_view<T>(S.rand, (uint32_t)N, relu, S.n);
                 if (relu) {
                     for (uint64_t e = b0 + threadIdx.x; e < b1; e += blockDim.x)
-                        drelu_pre_element<T, N, F, true, false>(X0, X1, Y0, Y1, nullptr, R, e, Index::of(base + b0, e - b0),
+                        drelu_pre_element<T, N, F, true, false, true>(X0, X1, Y0, Y1, nullptr, R, e, Index::of(base + b0, e - b0),
                                                                 mask, in_mask, k_in, A.k_lo, s02, s12, f);
                 } else {
                     for (uint64_t e = b0 + threadIdx.x; e < b1; e += blockDim.x)
-                        drelu_pre_element<T, N, F, false, false>(X0, X1, Y0, Y1, nullptr, R, e, Index::of(base + b0, e - b0),
+                        drelu_pre_element<T, N, F, false, false, true>(X0, X1, Y0, Y1, nullptr, R, e, Index::of(base + b0, e - b0),
                                                                  mask, in_mask, k_in, A.k_lo, s02, s12, f);
                 }
             } else if (S.op == BC_OP_RELU) {

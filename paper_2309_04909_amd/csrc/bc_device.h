@@ -45,6 +45,34 @@ __device__ __forceinline__ void st_nt(P* p, P v) {
     __builtin_nontemporal_store(v, p);
 }
 
+// A word of a record's or message's plane, around the L2 (NT) or through it.
+template <bool NT, typename P>
+__device__ __forceinline__ P ld_plane(const P* p) {
+    if constexpr (NT)
+        return ld_nt(p);
+    else
+        return *p;
+}
+template <bool NT, typename P>
+__device__ __forceinline__ void st_plane(P* p, P v) {
+    if constexpr (NT)
+        st_nt(p, v);
+    else
+        *p = v;
+}
+
+// The calling block's place in the walk over the elements: blockIdx, or with
+// BY_XCD an order in which the blocks of one XCD are neighbours (the hardware
+// deals blockIdx out to the 8 XCDs in turn), so that one L2 merges their
+// stores to a shared line.
+template <bool BY_XCD>
+__device__ __forceinline__ uint32_t walk_block() {
+    const uint32_t b = blockIdx.x;
+    if constexpr (!BY_XCD) return b;
+    const uint32_t x = b & 7u, per = gridDim.x >> 3, rest = gridDim.x & 7u;
+    return x * per + (x < rest ? x : rest) + (b >> 3);
+}
+
 constexpr uint32_t TAG_SHUFFLE = 1;
 constexpr uint32_t TAG_MASK = 2;
 constexpr uint32_t TAG_RESP = 3;

@@ -108,6 +108,30 @@ __host__ __device__ inline RandOffsets rand_offsets(uint32_t npos, bool relu, ui
     return o;
 }
 
+// How planes (the word-major arrays [planes][n] of a record or of packed
+// messages, `bytes` of them an element) are written and read.
+//
+// Written through the L2, by XCD: where n is no multiple of 32 the planes
+// start inside a 128-byte line, two waves share most lines, and around the L2
+// each line is two partial writes to memory.  Expansion, DReLU, us (around the
+// L2 in block order / through it by XCD), bytes an element in parentheses:
+//   N = 19 (116)  1,000,003 39 / 23   8,000,003 342 / 234   2^20 30 / 26   2^23 190 / 194
+//   N = 32 (288)  1,000,003 96 / 48   8,000,003 827 / 588   2^20 65 / 49   2^23 460 / 436
+//   N = 16 (80)   1,000,003 24 / 21   8,000,003 214 / 138   2^20 18.9 / 19.2
+// Up to 32 MB are then left in the L2s when the kernel ends, which costs small
+// records (bound by the VALU) more than it gives: N = 8 ReLU (32) 1,000,003
+// 14.6 / 16.7, 3,211,264 37 / 38.  Messages are read at once by the reply
+// (send + send + reply + finish, N = 19, 1,000,003: 77 / 73).
+constexpr bool planes_around_l2(uint64_t bytes) { return bytes < 48; }
+
+// Read by XCD through the L2 where the 256 MB memory-side cache holds most of
+// them, else around it in block order, so that the part which a writer just
+// left there is not evicted before it is read.  Expansion and online call,
+// N = 19, us (cached by XCD / around the L2 in block order):
+//   1,000,003 54 / 56   4,000,003 255 / 213   8,000,003 475 / 428   2^20 54 / 61   2^23 463 / 389
+// P2's reply alone: 1,000,003 16.8 / 20.0, 1,500,001 24.1 / 29.9, 4,000,003 83 / 81.
+inline bool planes_cached(uint64_t n, uint64_t bytes) { return n * bytes <= (320ull << 20); }
+
 // Fully validated replicated-sharing DReLU/ReLU launch (Alg. drelu2).
 struct RssLaunch {
     const void* x0;

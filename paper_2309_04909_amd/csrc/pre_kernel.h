@@ -62,18 +62,18 @@ struct RzLayout {
 };
 
 // Offline: expand the seeds of n elements into the record.
-template <typename T, int N, typename F, bool RELU>
+template <typename T, int N, typename F, bool RELU, bool NT>
 __global__ BC_KERNEL_ATTRS void k_expand(ExpandKArgs A, F f) {
     const T mask = (T)A.ring_mask;
     const uint64_t n = A.n;
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t e = A.begin + (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < A.end; e += stride) {
+    for (uint64_t e = A.begin + (uint64_t)walk_block<!NT>() * blockDim.x + threadIdx.x; e < A.end; e += stride) {
         const Index g = Index::of(A.elem_base + A.begin, e - A.begin);
         const StreamAt r01 = A.s01.at(g);
         uint32_t perm[(N + 3) / 4];
         const uint32_t t = shuffle_perm<N>(r01, perm);
 #pragma unroll
-        for (int k = 0; k < (N + 3) / 4; ++k) st_nt(&A.perm[(uint64_t)k * n + e], k == 0 ? perm[0] | t << 7 : perm[k]);
+        for (int k = 0; k < (N + 3) / 4; ++k) st_plane<NT>(&A.perm[(uint64_t)k * n + e], k == 0 ? perm[0] | t << 7 : perm[k]);
         MaskReader<N, F> masks;
         uint64_t* rz = static_cast<uint64_t*>(A.rz);
         constexpr int K = RzLayout<N>::K;
@@ -88,7 +88,7 @@ __global__ BC_KERNEL_ATTRS void k_expand(ExpandKArgs A, F f) {
                 const int v = 2 * j + h;
                 acc |= (uint64_t)(h ? z : r) << (N * (v % K) % 64);
                 if (v % K == K - 1 || v == 2 * N - 1) {
-                    st_nt(&rz[(uint64_t)(v / K) * n + e], acc);
+                    st_plane<NT>(&rz[(uint64_t)(v / K) * n + e], acc);
                     acc = 0;
                 }
             }
@@ -96,7 +96,7 @@ __global__ BC_KERNEL_ATTRS void k_expand(ExpandKArgs A, F f) {
         if constexpr (RELU) {
             T ba0, bb0, bc0, ba1, bb1;
             beaver_shares<T>(A.s02, A.s12, g, mask, ba0, bb0, bc0, ba1, bb1);
-            st_nt(&static_cast<T*>(A.tail)[e], (T)((T)((T)(ba0 + ba1) * (T)(bb0 + bb1) - bc0) & mask));   // P2's [c]_1
+            st_plane<NT>(&static_cast<T*>(A.tail)[e], (T)((T)((T)(ba0 + ba1) * (T)(bb0 + bb1) - bc0) & mask));   // P2's [c]_1
         }
     }
 }
@@ -123,7 +123,7 @@ __device__ __forceinline__ RecordView<T> record_view(const void* rand, uint32_t 
 // shares of Z_{2^(l + k_in)} truncated by k_in bits first, Alg. 5, as in
 // drelu_element) and writes Y0[e], Y1[e]; with CAP the round-1 messages go
 // to cap[e * N + slot] and cap[(R.n + e) * N + slot].
-template <typename T, int N, typename F, bool RELU, bool CAP>
+template <typename T, int N, typename F, bool RELU, bool CAP, bool NT>
 __device__ __forceinline__ void drelu_pre_element(const T* __restrict__ X0, const T* __restrict__ X1, T* Y0, T* Y1,
                                                   typename F::T* cap, const RecordView<T>& R, uint64_t e, Index g,
                                                   T mask, T in_mask, uint32_t k_in, uint32_t k_lo, const Stream& s02,
@@ -134,7 +134,7 @@ __device__ __forceinline__ void drelu_pre_element(const T* __restrict__ X0, cons
     input_shares<T>(ld_nt(&X0[e]), ld_nt(&X1[e]), mask, in_mask, k_in, in0, n1);
     uint32_t perm[(N + 3) / 4];
 #pragma unroll
-    for (int k = 0; k < (N + 3) / 4; ++k) perm[k] = ld_nt(&R.perm[(uint64_t)k * n + e]);
+    for (int k = 0; k < (N + 3) / 4; ++k) perm[k] = ld_plane<NT>(&R.perm[(uint64_t)k * n + e]);
     const uint32_t t = (perm[0] >> 7) & 1u;
     const T a0 = flip_by(in0, t, mask);                // the flip, as in drelu_round1
     const T nb1 = flip_by(n1, t, mask);
@@ -150,7 +150,7 @@ __device__ __forceinline__ void drelu_pre_element(const T* __restrict__ X0, cons
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int v = 2 * j + h;
-            if (v % K == 0) cur = ld_nt(&R.rz[(uint64_t)(v / K) * n + e]);
+            if (v % K == 0) cur = ld_plane<NT>(&R.rz[(uint64_t)(v / K) * n + e]);
             rv[h] = (FT)((cur >> (N * (v % K) % 64)) & RzLayout<N>::FIELD);
         }
         const FT r = rv[0], z = rv[1];
@@ -177,14 +177,14 @@ __device__ __forceinline__ void drelu_pre_element(const T* __restrict__ X0, cons
         const T in1 = (T)((T)0 - n1) & mask;
         T ba0, bb0, bc0, ba1, bb1;                                  // the parties' triple shares, regenerated
         beaver_shares<T>(s02, s12, g, mask, ba0, bb0, bc0, ba1, bb1);
-        relu_finish<T>(dp, in0, in1, ba0, bb0, bc0, ba1, bb1, ld_nt(&R.tail[e]), t, mask, y0, y1);
+        relu_finish<T>(dp, in0, in1, ba0, bb0, bc0, ba1, bb1, ld_plane<NT>(&R.tail[e]), t, mask, y0, y1);
     }
     st_nt(&Y0[e], y0);
     st_nt(&Y1[e], y1);
 }
 
 // Online call: grid-stride over the n elements of one share pair.
-template <typename T, int N, typename F, bool RELU, bool CAP>
+template <typename T, int N, typename F, bool RELU, bool CAP, bool NT>
 __device__ __forceinline__ void drelu_pre_loop(const PreKArgs& A, const F& f, T mask) {
     const T* X0 = static_cast<const T*>(A.x0);
     const T* X1 = static_cast<const T*>(A.x1);
@@ -193,29 +193,48 @@ __device__ __forceinline__ void drelu_pre_loop(const PreKArgs& A, const F& f, T 
     typename F::T* cap = static_cast<typename F::T*>(A.cap);
     const RecordView<T> R{A.perm, static_cast<const uint64_t*>(A.rz), static_cast<const T*>(A.tail), A.n};
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t e = A.begin + (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < A.end; e += stride)
-        drelu_pre_element<T, N, F, RELU, CAP>(X0, X1, Y0, Y1, cap, R, e, Index::of(A.elem_base + A.begin, e - A.begin), mask, mask, 0, A.k_lo,
+    for (uint64_t e = A.begin + (uint64_t)walk_block<!NT>() * blockDim.x + threadIdx.x; e < A.end; e += stride)
+        drelu_pre_element<T, N, F, RELU, CAP, NT>(X0, X1, Y0, Y1, cap, R, e, Index::of(A.elem_base + A.begin, e - A.begin), mask, mask, 0, A.k_lo,
                                               A.s02, A.s12, f);
 }
 
 // On a full-width ring the loop runs with the ring mask as a constant (see
 // k_drelu).
-template <typename T, int N, typename F, bool RELU, bool CAP>
+template <typename T, int N, typename F, bool RELU, bool CAP, bool NT>
 __global__ BC_KERNEL_ATTRS void k_drelu_pre(PreKArgs A, F f_arg) {
     const F f = f_arg.vgpr();
     if constexpr (!CAP) {
         if ((T)A.ring_mask == (T)~(T)0) {
-            drelu_pre_loop<T, N, F, RELU, CAP>(A, f, (T)~(T)0);
+            drelu_pre_loop<T, N, F, RELU, CAP, NT>(A, f, (T)~(T)0);
             return;
         }
     }
-    drelu_pre_loop<T, N, F, RELU, CAP>(A, f, in_vgpr((T)A.ring_mask));
+    drelu_pre_loop<T, N, F, RELU, CAP, NT>(A, f, in_vgpr((T)A.ring_mask));
 }
 
-template <typename T, int N, typename F>
+template <typename T, int N, typename F, bool RELU, bool NT>
+hipError_t launch_expand(const PreLaunch& L, ExpandKArgs A, const F& f, hipStream_t st) {
+    return by_index_range(L.elem_base, L.n, [&](uint64_t begin, uint64_t end) {
+        A.begin = begin;
+        A.end = end;
+        hipLaunchKernelGGL((k_expand<T, N, F, RELU, NT>), dim3(L.grid), dim3(256), 0, st, A, f);
+    });
+}
+
+template <typename T, int N, typename F, bool RELU, bool CAP, bool NT>
+hipError_t launch_pre(const PreLaunch& L, PreKArgs A, const F& f, hipStream_t st) {
+    return by_index_range(L.elem_base, L.n, [&](uint64_t begin, uint64_t end) {
+        A.begin = begin;
+        A.end = end;
+        hipLaunchKernelGGL((k_drelu_pre<T, N, F, RELU, CAP, NT>), dim3(L.grid), dim3(256), 0, st, A, f);
+    });
+}
+
+template <typename T, int N, typename F, bool RELU>
 hipError_t launch_pre_field(const PreLaunch& L, const F& f, hipStream_t st) {
     const uint64_t mask = L.ell >= 64 ? ~0ull : ((1ull << L.ell) - 1);
-    const RandOffsets o = rand_offsets(N, L.relu, sizeof(T), L.n);
+    const RandOffsets o = rand_offsets(N, RELU, sizeof(T), L.n);
+    constexpr uint64_t bytes = 4 * ((N + 3) / 4) + 8 * rz_words(N) + (RELU ? sizeof(T) : 0);   // of record an element
     uint8_t* base = static_cast<uint8_t*>(L.rand);
     if (L.expand) {
         ExpandKArgs A;
@@ -228,14 +247,7 @@ hipError_t launch_pre_field(const PreLaunch& L, const F& f, hipStream_t st) {
         A.s01 = Stream{L.s01.k0, L.s01.k1, L.s01.n0, L.s01.n1};
         A.s02 = Stream{L.s02.k0, L.s02.k1, L.s02.n0, L.s02.n1};
         A.s12 = Stream{L.s12.k0, L.s12.k1, L.s12.n0, L.s12.n1};
-        return by_index_range(L.elem_base, L.n, [&](uint64_t begin, uint64_t end) {
-            A.begin = begin;
-            A.end = end;
-            if (L.relu)
-                hipLaunchKernelGGL((k_expand<T, N, F, true>), dim3(L.grid), dim3(256), 0, st, A, f);
-            else
-                hipLaunchKernelGGL((k_expand<T, N, F, false>), dim3(L.grid), dim3(256), 0, st, A, f);
-        });
+        return launch_expand<T, N, F, RELU, planes_around_l2(bytes)>(L, A, f, st);
     }
     PreKArgs A;
     A.x0 = L.x0;
@@ -253,22 +265,17 @@ hipError_t launch_pre_field(const PreLaunch& L, const F& f, hipStream_t st) {
     A.pad = 0;
     A.s02 = Stream{L.s02.k0, L.s02.k1, L.s02.n0, L.s02.n1};
     A.s12 = Stream{L.s12.k0, L.s12.k1, L.s12.n0, L.s12.n1};
-    return by_index_range(L.elem_base, L.n, [&](uint64_t begin, uint64_t end) {
-        A.begin = begin;
-        A.end = end;
-        if (L.relu) {
-            if (L.cap) hipLaunchKernelGGL((k_drelu_pre<T, N, F, true, true>), dim3(L.grid), dim3(256), 0, st, A, f);
-            else hipLaunchKernelGGL((k_drelu_pre<T, N, F, true, false>), dim3(L.grid), dim3(256), 0, st, A, f);
-        } else {
-            if (L.cap) hipLaunchKernelGGL((k_drelu_pre<T, N, F, false, true>), dim3(L.grid), dim3(256), 0, st, A, f);
-            else hipLaunchKernelGGL((k_drelu_pre<T, N, F, false, false>), dim3(L.grid), dim3(256), 0, st, A, f);
-        }
-    });
+    if (L.cap) return launch_pre<T, N, F, RELU, true, true>(L, A, f, st);
+    if constexpr (!planes_around_l2(bytes))
+        if (planes_cached(L.n, bytes)) return launch_pre<T, N, F, RELU, false, false>(L, A, f, st);
+    return launch_pre<T, N, F, RELU, false, true>(L, A, f, st);
 }
 
 template <typename T, int N>
 hipError_t launch_pre_exact(const PreLaunch& L, hipStream_t st) {
-    return with_field<N>(L.p, [&](auto f) { return launch_pre_field<T, N, decltype(f)>(L, f, st); });
+    return with_field<N>(L.p, [&](auto f) {
+        return L.relu ? launch_pre_field<T, N, decltype(f), true>(L, f, st) : launch_pre_field<T, N, decltype(f), false>(L, f, st);
+    });
 }
 
 template <typename T, int NLO, int NHI>

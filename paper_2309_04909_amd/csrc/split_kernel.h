@@ -75,7 +75,7 @@ __global__ BC_KERNEL_ATTRS void k_send(SplitKArgs A, F f_arg) {
     uint32_t* M = static_cast<uint32_t*>(A.out0);
     const T mask = in_vgpr((T)A.ring_mask);
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t e = A.begin + (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < A.end; e += stride) {
+    for (uint64_t e = A.begin + (uint64_t)walk_block<true>() * blockDim.x + threadIdx.x; e < A.end; e += stride) {
         const Index g = Index::of(A.elem_base + A.begin, e - A.begin);
         const T x = X[e] & mask;
         const StreamAt r01 = A.s01.at(g);
@@ -95,11 +95,11 @@ __global__ BC_KERNEL_ATTRS void k_send(SplitKArgs A, F f_arg) {
             pack_slot<N>(words, j, (uint64_t)party_message<T, N, F, PARTY>(ak, sig.pos(j), sig.times(j), r, z, f));
         }
 #pragma unroll
-        for (int k = 0; k < W; ++k) st_nt(&M[(uint64_t)k * A.n + e], words[k]);
+        for (int k = 0; k < W; ++k) M[(uint64_t)k * A.n + e] = words[k];   // through the L2, by XCD: see planes_around_l2
     }
 }
 
-template <typename T, int N, typename F>
+template <typename T, int N, typename F, bool NT>
 __global__ BC_KERNEL_ATTRS void k_reply(SplitKArgs A, F f_arg) {
     using FT = typename F::T;
     constexpr int W = Packing<N>::W;
@@ -110,12 +110,12 @@ __global__ BC_KERNEL_ATTRS void k_reply(SplitKArgs A, F f_arg) {
     T* D1 = static_cast<T*>(A.out1);
     const T mask = in_vgpr((T)A.ring_mask);
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t e = A.begin + (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < A.end; e += stride) {
+    for (uint64_t e = A.begin + (uint64_t)walk_block<!NT>() * blockDim.x + threadIdx.x; e < A.end; e += stride) {
         uint32_t w0[W], w1[W];
 #pragma unroll
         for (int k = 0; k < W; ++k) {
-            w0[k] = ld_nt(&M0[(uint64_t)k * A.n + e]);
-            w1[k] = ld_nt(&M1[(uint64_t)k * A.n + e]);
+            w0[k] = ld_plane<NT>(&M0[(uint64_t)k * A.n + e]);
+            w1[k] = ld_plane<NT>(&M1[(uint64_t)k * A.n + e]);
         }
         FT least = f.p;
 #pragma unroll
@@ -163,21 +163,36 @@ inline SplitKArgs make_split_kargs(const SplitLaunch& L) {
     return A;
 }
 
+template <typename T, int N, typename F>
+hipError_t launch_send(const SplitLaunch& L, SplitKArgs A, const F& f, hipStream_t st) {
+    return by_index_range(L.elem_base, L.n, [&](uint64_t begin, uint64_t end) {
+        A.begin = begin;
+        A.end = end;
+        if (L.party == 0)
+            hipLaunchKernelGGL((k_send<T, N, F, 0>), dim3(L.grid), dim3(256), 0, st, A, f);
+        else
+            hipLaunchKernelGGL((k_send<T, N, F, 1>), dim3(L.grid), dim3(256), 0, st, A, f);
+    });
+}
+
+template <typename T, int N, typename F, bool NT>
+hipError_t launch_reply(const SplitLaunch& L, SplitKArgs A, const F& f, hipStream_t st) {
+    return by_index_range(L.elem_base, L.n, [&](uint64_t begin, uint64_t end) {
+        A.begin = begin;
+        A.end = end;
+        hipLaunchKernelGGL((k_reply<T, N, F, NT>), dim3(L.grid), dim3(256), 0, st, A, f);
+    });
+}
+
 template <typename T, int N>
 hipError_t launch_split_exact(const SplitLaunch& L, hipStream_t st) {
-    SplitKArgs A = make_split_kargs(L);
+    constexpr uint64_t bytes = 4 * Packing<N>::W;          // of one message an element
+    const SplitKArgs A = make_split_kargs(L);
     return with_field<N>(L.p, [&](auto f) {
         using F = decltype(f);
-        return by_index_range(L.elem_base, L.n, [&](uint64_t begin, uint64_t end) {
-            A.begin = begin;
-            A.end = end;
-            if (L.kind == SplitLaunch::SEND && L.party == 0)
-                hipLaunchKernelGGL((k_send<T, N, F, 0>), dim3(L.grid), dim3(256), 0, st, A, f);
-            else if (L.kind == SplitLaunch::SEND)
-                hipLaunchKernelGGL((k_send<T, N, F, 1>), dim3(L.grid), dim3(256), 0, st, A, f);
-            else
-                hipLaunchKernelGGL((k_reply<T, N, F>), dim3(L.grid), dim3(256), 0, st, A, f);
-        });
+        if (L.kind == SplitLaunch::SEND) return launch_send<T, N, F>(L, A, f, st);
+        return planes_cached(L.n, 2 * bytes) ? launch_reply<T, N, F, false>(L, A, f, st)
+                                             : launch_reply<T, N, F, true>(L, A, f, st);
     });
 }
 

@@ -204,8 +204,13 @@ std::atomic<uint32_t> g_sched[kKinds][34][2][2];
 // kernels; eight times as many let it take the next block as one ends instead
 // of waiting for the slowest walk of a persistent block.  Ragged batch of
 // 9,232,384 elements at 8 / 16 / 64: l_x = 18 209 / 198 / 197 us, l_x = 11
-// (l = 51) 167 / 158 / 155, l_x = 8 (l = 32) 134 / 124 / 121.
-constexpr uint32_t kDefaultBpc[kKinds] = {16, 8, 16, 16, 64, 8, 2};
+// (l = 51) 167 / 158 / 155, l_x = 8 (l = 32) 134 / 124 / 121; ReLU, its record's
+// expansion and its online call at l_x = 15, 4,000,003 elements, 16 / 64: 77 / 78,
+// 125 / 110, 92 / 82 (l_x = 23: 104 / 101, 320 / 292, 207 / 193).  Streaming calls
+// are bound by memory, which is fastest when all blocks walk it in one order
+// without a stride: truncation at l = 64, 2^26 elements, 64 / 256 / 1024: 409 /
+// 365 / 338 us; 2^24 84.8 / 82.6 / 82.3.
+constexpr uint32_t kDefaultBpc[kKinds] = {64, 1024, 64, 64, 64, 8, 2};
 
 uint32_t sched_value(uint32_t kind, uint32_t npos, uint32_t width, bool relu) {
     const uint32_t v =

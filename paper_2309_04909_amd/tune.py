@@ -205,7 +205,7 @@ def tune_stream(n, reps):
     x0, x1 = _shares(n, 64, 9)
     y0, y1 = torch.empty_like(x0), torch.empty_like(x1)
     best = None
-    for bpc in BPC:
+    for bpc in BPC + [256, 1024]:
         B.set_schedule("stream", 0, bpc, 8)
         ms = _time(lambda: B.trunc_det(x0, x1, 64, 13, out=(y0, y1)), reps)
         print(f"  stream bpc={bpc:3d}: {ms:.4f} ms ({32 * n / ms / 1e6:.0f} GB/s)", flush=True)

@@ -88,15 +88,18 @@ __device__ __forceinline__ void batch_walk(const bc_segment* __restrict__ segs,
                 // precomputed randomness: the segment's record replaces its seed_01
                 // draws (and holds P2's [c]_1); seed_02 / seed_12 draws are regenerated
                 const bool relu = S.op == BC_OP_RELU;
-                const RecordView<T> R = record_view<T>(S.rand, (uint32_t)N, relu, S.n);
+                const RecordView<T> R = record_view<T>(S.rand, (uint32_t)N, relu, S.n).from(b0);
+                const uint32_t m = (uint32_t)(b1 - b0);
                 if (relu) {
-                    for (uint64_t e = b0 + threadIdx.x; e < b1; e += blockDim.x)
-                        drelu_pre_element<T, N, F, true, false, true>(X0, X1, Y0, Y1, nullptr, R, e, Index::of(base + b0, e - b0),
-                                                                mask, in_mask, k_in, A.k_lo, s02, s12, f);
+                    for (uint32_t i = threadIdx.x; i < m; i += blockDim.x)
+                        drelu_pre_element<T, N, F, true, false, true>(X0 + b0, X1 + b0, Y0 + b0, Y1 + b0, nullptr, R, i,
+                                                                      Index::of(base + b0, i), mask, in_mask, k_in,
+                                                                      A.k_lo, s02, s12, f);
                 } else {
-                    for (uint64_t e = b0 + threadIdx.x; e < b1; e += blockDim.x)
-                        drelu_pre_element<T, N, F, false, false, true>(X0, X1, Y0, Y1, nullptr, R, e, Index::of(base + b0, e - b0),
-                                                                 mask, in_mask, k_in, A.k_lo, s02, s12, f);
+                    for (uint32_t i = threadIdx.x; i < m; i += blockDim.x)
+                        drelu_pre_element<T, N, F, false, false, true>(X0 + b0, X1 + b0, Y0 + b0, Y1 + b0, nullptr, R, i,
+                                                                       Index::of(base + b0, i), mask, in_mask, k_in,
+                                                                       A.k_lo, s02, s12, f);
                 }
             } else if (S.op == BC_OP_RELU) {
                 tile_elements<T, N, F, true>(X0, X1, Y0, Y1, b0, b1, base, mask, in_mask, k_in, A.k_lo, s01, s02, s12, f);

@@ -11,6 +11,7 @@
 //      Field64     p < 2^34   l_x = 32; 66-bit products, fp64 quotient
 #pragma once
 
+#include <type_traits>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -45,6 +46,29 @@ __device__ __forceinline__ void st_nt(P* p, P v) {
     __builtin_nontemporal_store(v, p);
 }
 
+// Elements of one launch: at most 2^28, so that element indices and byte
+// offsets (and an index plus the grid's stride) stay in 32 bits; the host runs
+// a larger call, or one whose global index passes a multiple of 2^32, as
+// launches over consecutive ranges, each with its own element offset, which
+// gives the results of one launch.
+constexpr uint64_t kLaunchElems = 1ull << 28;
+
+// Element i of p, addressed as p plus a 32-bit byte offset (the load or
+// store then takes p from scalar registers and the offset from one VGPR).
+template <typename T>
+__device__ __forceinline__ T* elem_at(T* p, uint32_t i) {
+    using Byte = typename std::conditional<std::is_const<T>::value, const char, char>::type;
+    return reinterpret_cast<T*>(reinterpret_cast<Byte*>(p) + (uint32_t)(i * (uint32_t)sizeof(T)));
+}
+// Nontemporal (ld_nt / st_nt).
+template <typename T>
+__device__ __forceinline__ T load_at(const T* p, uint32_t i) {
+    return ld_nt(elem_at(p, i));
+}
+template <typename T>
+__device__ __forceinline__ void store_at(T* p, uint32_t i, T v) {
+    st_nt(elem_at(p, i), v);
+}
 // A word of a record's or message's plane, around the L2 (NT) or through it.
 template <bool NT, typename P>
 __device__ __forceinline__ P ld_plane(const P* p) {
@@ -60,6 +84,21 @@ __device__ __forceinline__ void st_plane(P* p, P v) {
     else
         *p = v;
 }
+
+// The planes [0, 1, ...][n] from p, in turn.  The step is opaque, so that a
+// loop over the elements keeps one pointer and not one per plane (which do
+// not fit the scalar registers).
+template <typename P>
+struct Planes {
+    P* at;
+    uint64_t n;
+    __device__ __forceinline__ P* next() {
+        P* p = at;
+        at += n;
+        asm("" : "+s"(at));
+        return p;
+    }
+};
 
 // The calling block's place in the walk over the elements: blockIdx, or with
 // BY_XCD an order in which the blocks of one XCD are neighbours (the hardware

@@ -813,25 +813,6 @@ __device__ __forceinline__ void drelu_element(const T* __restrict__ X0, const T*
     st_nt(&Y1[e], y1);
 }
 
-// Elements of one k_drelu launch: at most 2^28, so that element indices and
-// byte offsets (and an index plus the grid's stride) stay in 32 bits; the
-// host runs a larger call, or one whose global index passes a multiple of
-// 2^32, as launches over consecutive ranges, each with its own element
-// offset, which gives the results of one launch.
-constexpr uint64_t kLaunchElems = 1ull << 28;
-
-// Element i of p, addressed as p plus a 32-bit byte offset (the load or
-// store then takes p from scalar registers and the offset from one VGPR),
-// nontemporal (ld_nt / st_nt).
-template <typename T>
-__device__ __forceinline__ T load_at(const T* p, uint32_t i) {
-    return ld_nt(reinterpret_cast<const T*>(reinterpret_cast<const char*>(p) + (uint32_t)(i * (uint32_t)sizeof(T))));
-}
-template <typename T>
-__device__ __forceinline__ void store_at(T* p, uint32_t i, T v) {
-    st_nt(reinterpret_cast<T*>(reinterpret_cast<char*>(p) + (uint32_t)(i * (uint32_t)sizeof(T))), v);
-}
-
 // Element i of the buffer r (a raw buffer of 4- or 8-byte elements), loaded
 // nontemporal; an element past the buffer's end reads as 0 without a memory
 // access (the buffer's range check).
@@ -1074,13 +1055,14 @@ inline DreluKArgs make_kargs(const DreluLaunch& L) {
     return A;
 }
 
-// Calls launch(begin, end) for the consecutive ranges of n elements that share
-// the high word of their global index (one, unless it passes a multiple of
-// 2^32), and returns the first launch error.
+// Calls launch(begin, end) for the consecutive ranges of n elements of at most
+// kLaunchElems that share the high word of their global index, and returns the
+// first launch error.
 template <typename Fn>
 hipError_t by_index_range(uint64_t elem_base, uint64_t n, Fn&& launch) {
     for (uint64_t begin = 0, end; begin < n; begin = end) {
         end = index_end(elem_base, begin, n);
+        if (end - begin > kLaunchElems) end = begin + kLaunchElems;
         launch(begin, end);
         const hipError_t err = hipGetLastError();
         if (err != hipSuccess) return err;

@@ -61,23 +61,39 @@ struct RzLayout {
     static constexpr uint64_t FIELD = WIDE ? ~0ull : (1ull << N) - 1;
 };
 
-// Offline: expand the seeds of n elements into the record.
+// Puts a field of `width` bits at bit `off` of the 64-bit word w (off and width
+// compile-time after unrolling).  The field is opaque: the compiler would cut
+// a value that is the high word of a product out of the 64-bit product, with a
+// shift and a mask, where one shift-or is enough.
+__device__ __forceinline__ void pack_field(uint32_t (&w)[2], int off, uint32_t v, int width) {
+    asm("" : "+v"(v));
+    const int q = off / 32, sh = off % 32;
+    w[q] |= v << sh;
+    if (sh + width > 32 && q == 0) w[1] |= v >> (32 - sh);
+}
+
+// Offline: expand the seeds of n elements into the record.  Bound by VALU
+// issue up to N = 9 (N = 8 ReLU: 364 instructions, 264 of them Philox; 388
+// with 64-bit element addresses and the fields cut out of their products:
+// 3,211,264 elements 39.7 -> 37.8 us) and by the writes of the planes from
+// N = 16 on (5.3-5.8 TB/s through the L2, see planes_around_l2).
 template <typename T, int N, typename F, bool RELU, bool NT>
 __global__ BC_KERNEL_ATTRS void k_expand(ExpandKArgs A, F f) {
     const T mask = (T)A.ring_mask;
     const uint64_t n = A.n;
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t e = A.begin + (uint64_t)walk_block<!NT>() * blockDim.x + threadIdx.x; e < A.end; e += stride) {
-        const Index g = Index::of(A.elem_base + A.begin, e - A.begin);
+    const uint32_t count = (uint32_t)(A.end - A.begin), stride = gridDim.x * blockDim.x;   // at most kLaunchElems
+    for (uint32_t i = walk_block<!NT>() * blockDim.x + threadIdx.x; i < count; i += stride) {
+        const Index g = Index::of(A.elem_base + A.begin, i);
         const StreamAt r01 = A.s01.at(g);
+        Planes<uint32_t> perms{A.perm + A.begin, n};
+        Planes<uint64_t> rzs{static_cast<uint64_t*>(A.rz) + A.begin, n};
         uint32_t perm[(N + 3) / 4];
         const uint32_t t = shuffle_perm<N>(r01, perm);
 #pragma unroll
-        for (int k = 0; k < (N + 3) / 4; ++k) st_plane<NT>(&A.perm[(uint64_t)k * n + e], k == 0 ? perm[0] | t << 7 : perm[k]);
+        for (int k = 0; k < (N + 3) / 4; ++k) st_plane<NT>(elem_at(perms.next(), i), k == 0 ? perm[0] | t << 7 : perm[k]);
         MaskReader<N, F> masks;
-        uint64_t* rz = static_cast<uint64_t*>(A.rz);
         constexpr int K = RzLayout<N>::K;
-        uint64_t acc = 0;                                  // the word being filled
+        uint32_t acc[2] = {0, 0};                          // the word being filled, low half first
 #pragma unroll
         for (int j = 0; j < N; ++j) {
             typename F::T r, z;
@@ -86,17 +102,20 @@ __global__ BC_KERNEL_ATTRS void k_expand(ExpandKArgs A, F f) {
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const int v = 2 * j + h;
-                acc |= (uint64_t)(h ? z : r) << (N * (v % K) % 64);
-                if (v % K == K - 1 || v == 2 * N - 1) {
-                    st_plane<NT>(&rz[(uint64_t)(v / K) * n + e], acc);
-                    acc = 0;
+                if constexpr (RzLayout<N>::WIDE)
+                    st_plane<NT>(elem_at(rzs.next(), i), (uint64_t)(h ? z : r));
+                else
+                    pack_field(acc, N * (v % K), (uint32_t)(h ? z : r), N);
+                if (!RzLayout<N>::WIDE && (v % K == K - 1 || v == 2 * N - 1)) {
+                    st_plane<NT>(elem_at(rzs.next(), i), join64(acc[0], acc[1]));
+                    acc[0] = acc[1] = 0;
                 }
             }
         }
         if constexpr (RELU) {
             T ba0, bb0, bc0, ba1, bb1;
             beaver_shares<T>(A.s02, A.s12, g, mask, ba0, bb0, bc0, ba1, bb1);
-            st_plane<NT>(&static_cast<T*>(A.tail)[e], (T)((T)((T)(ba0 + ba1) * (T)(bb0 + bb1) - bc0) & mask));   // P2's [c]_1
+            st_plane<NT>(elem_at(static_cast<T*>(A.tail) + A.begin, i), (T)((T)((T)(ba0 + ba1) * (T)(bb0 + bb1) - bc0) & mask));   // P2's [c]_1
         }
     }
 }
@@ -108,6 +127,10 @@ struct RecordView {
     const uint64_t* rz;
     const T* tail;
     uint64_t n;
+    // The same record from element `begin`.
+    __device__ __forceinline__ RecordView from(uint64_t begin) const {
+        return RecordView{perm + begin, rz + begin, tail + begin, n};
+    }
 };
 
 template <typename T>
@@ -118,23 +141,29 @@ __device__ __forceinline__ RecordView<T> record_view(const void* rand, uint32_t 
                          reinterpret_cast<const T*>(base + o.tail), n};
 }
 
-// Online: the input-dependent part of Alg. 7 (and of Alg. 8) for element e,
-// reading its draws from the record.  Reads X0[e], X1[e] (with k_in > 0,
+// Online: bound by the reads of the record and the shares (N = 8 ReLU, 64 bytes
+// an element: 3,211,264 elements 37 us, 5.5 TB/s; N = 19: 5.0 TB/s).  Element
+// addresses are 32-bit offsets from scalar pointers (305 -> 302 instructions).
+// The input-dependent part of Alg. 7 (and of Alg. 8) for element i of
+// a range (every pointer, and the record's, at the range's start), reading its
+// draws from the record.  Reads X0[i], X1[i] (with k_in > 0,
 // shares of Z_{2^(l + k_in)} truncated by k_in bits first, Alg. 5, as in
-// drelu_element) and writes Y0[e], Y1[e]; with CAP the round-1 messages go
-// to cap[e * N + slot] and cap[(R.n + e) * N + slot].
+// drelu_element) and writes Y0[i], Y1[i]; with CAP the round-1 messages go
+// to cap[i * N + slot] and cap[(R.n + i) * N + slot].
 template <typename T, int N, typename F, bool RELU, bool CAP, bool NT>
 __device__ __forceinline__ void drelu_pre_element(const T* __restrict__ X0, const T* __restrict__ X1, T* Y0, T* Y1,
-                                                  typename F::T* cap, const RecordView<T>& R, uint64_t e, Index g,
+                                                  typename F::T* cap, const RecordView<T>& R, uint32_t i, Index g,
                                                   T mask, T in_mask, uint32_t k_in, uint32_t k_lo, const Stream& s02,
                                                   const Stream& s12, const F& f) {
     using FT = typename F::T;
     const uint64_t n = R.n;
     T in0, n1;
-    input_shares<T>(ld_nt(&X0[e]), ld_nt(&X1[e]), mask, in_mask, k_in, in0, n1);
+    input_shares<T>(load_at(X0, i), load_at(X1, i), mask, in_mask, k_in, in0, n1);
+    Planes<const uint32_t> perms{R.perm, n};
+    Planes<const uint64_t> rzs{R.rz, n};
     uint32_t perm[(N + 3) / 4];
 #pragma unroll
-    for (int k = 0; k < (N + 3) / 4; ++k) perm[k] = ld_plane<NT>(&R.perm[(uint64_t)k * n + e]);
+    for (int k = 0; k < (N + 3) / 4; ++k) perm[k] = ld_plane<NT>(elem_at(perms.next(), i));
     const uint32_t t = (perm[0] >> 7) & 1u;
     const T a0 = flip_by(in0, t, mask);                // the flip, as in drelu_round1
     const T nb1 = flip_by(n1, t, mask);
@@ -150,7 +179,7 @@ __device__ __forceinline__ void drelu_pre_element(const T* __restrict__ X0, cons
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int v = 2 * j + h;
-            if (v % K == 0) cur = ld_plane<NT>(&R.rz[(uint64_t)(v / K) * n + e]);
+            if (v % K == 0) cur = ld_plane<NT>(elem_at(rzs.next(), i));
             rv[h] = (FT)((cur >> (N * (v % K) % 64)) & RzLayout<N>::FIELD);
         }
         const FT r = rv[0], z = rv[1];
@@ -160,8 +189,8 @@ __device__ __forceinline__ void drelu_pre_element(const T* __restrict__ X0, cons
         if constexpr (CAP) {
             FT w0, w1;
             slot_messages<F>(v0, v1, r, z, f, w0, w1);
-            cap[e * N + j] = w0;
-            cap[(n + e) * N + j] = w1;
+            cap[(uint64_t)i * N + j] = w0;
+            cap[(n + i) * N + j] = w1;
             const FT w = addmod(w0, w1, f);
             p2.take(j, w == 0 ? 0u : 0xFFFFFFFFu);
         } else {
@@ -177,24 +206,25 @@ __device__ __forceinline__ void drelu_pre_element(const T* __restrict__ X0, cons
         const T in1 = (T)((T)0 - n1) & mask;
         T ba0, bb0, bc0, ba1, bb1;                                  // the parties' triple shares, regenerated
         beaver_shares<T>(s02, s12, g, mask, ba0, bb0, bc0, ba1, bb1);
-        relu_finish<T>(dp, in0, in1, ba0, bb0, bc0, ba1, bb1, ld_plane<NT>(&R.tail[e]), t, mask, y0, y1);
+        relu_finish<T>(dp, in0, in1, ba0, bb0, bc0, ba1, bb1, ld_plane<NT>(elem_at(R.tail, i)), t, mask, y0, y1);
     }
-    st_nt(&Y0[e], y0);
-    st_nt(&Y1[e], y1);
+    store_at(Y0, i, y0);
+    store_at(Y1, i, y1);
 }
 
 // Online call: grid-stride over the n elements of one share pair.
 template <typename T, int N, typename F, bool RELU, bool CAP, bool NT>
 __device__ __forceinline__ void drelu_pre_loop(const PreKArgs& A, const F& f, T mask) {
-    const T* X0 = static_cast<const T*>(A.x0);
-    const T* X1 = static_cast<const T*>(A.x1);
-    T* Y0 = static_cast<T*>(A.y0);
-    T* Y1 = static_cast<T*>(A.y1);
+    const T* X0 = static_cast<const T*>(A.x0) + A.begin;
+    const T* X1 = static_cast<const T*>(A.x1) + A.begin;
+    T* Y0 = static_cast<T*>(A.y0) + A.begin;
+    T* Y1 = static_cast<T*>(A.y1) + A.begin;
     typename F::T* cap = static_cast<typename F::T*>(A.cap);
-    const RecordView<T> R{A.perm, static_cast<const uint64_t*>(A.rz), static_cast<const T*>(A.tail), A.n};
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t e = A.begin + (uint64_t)walk_block<!NT>() * blockDim.x + threadIdx.x; e < A.end; e += stride)
-        drelu_pre_element<T, N, F, RELU, CAP, NT>(X0, X1, Y0, Y1, cap, R, e, Index::of(A.elem_base + A.begin, e - A.begin), mask, mask, 0, A.k_lo,
+    if constexpr (CAP) cap += A.begin * N;
+    const RecordView<T> R = RecordView<T>{A.perm, static_cast<const uint64_t*>(A.rz), static_cast<const T*>(A.tail), A.n}.from(A.begin);
+    const uint32_t count = (uint32_t)(A.end - A.begin), stride = gridDim.x * blockDim.x;   // at most kLaunchElems
+    for (uint32_t i = walk_block<!NT>() * blockDim.x + threadIdx.x; i < count; i += stride)
+        drelu_pre_element<T, N, F, RELU, CAP, NT>(X0, X1, Y0, Y1, cap, R, i, Index::of(A.elem_base + A.begin, i), mask, mask, 0, A.k_lo,
                                               A.s02, A.s12, f);
 }
 

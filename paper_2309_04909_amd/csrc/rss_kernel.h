@@ -25,6 +25,10 @@
 // ReLU product (V_7..V_9).  [s]_2 = (w0, w1) of block 0 of TAG_RSS under
 // seed_12; s = bit 0 of word 0 of block 0 of TAG_RSS under seed_2.
 //
+// Bound by VALU issue (N = 19 ReLU: 989 instructions, 495 of them the 15
+// Philox blocks; 4,000,003 elements 106 us, 124 before the slots' test without
+// reductions, the sign as xor and add and 32-bit element addresses).
+//
 // Arithmetic in the storage width (2^64 or 2^32) reduces consistently mod
 // 2^l, so only the Alg. 7 inputs and the stored outputs are masked.
 #pragma once
@@ -66,14 +70,14 @@ __device__ __forceinline__ T word_pair(uint32_t lo, uint32_t hi) {
 template <typename T, int N, typename F, bool RELU, bool CAP>
 __device__ __forceinline__ void rss_element(const RssKArgs& A, const T* __restrict__ X0, const T* __restrict__ X1,
                                             const T* __restrict__ X2, T* Y0, T* Y1, T* Y2,
-                                            typename F::T* cap, uint64_t e, Index g, T mask, const F& f) {
-    const T x[3] = {ld_nt(&X0[e]), ld_nt(&X1[e]), ld_nt(&X2[e])};
+                                            typename F::T* cap, uint32_t i, Index g, T mask, const F& f) {
+    const T x[3] = {load_at(X0, i), load_at(X1, i), load_at(X2, i)};
 
     // round 1 and P2's zero test on the 2-of-2 input ([x]_0 + [x]_1, [x]_2),
     // whose second holder cuts its negated share -[x]_2
     uint32_t t;
     const T nx2 = (T)((T)0 - x[2]) & mask;
-    const T dp = drelu_round1<T, N, F, CAP>((T)(x[0] + x[1]) & mask, nx2, g, mask, A.k_lo, A.s01, cap, A.n, e, f, t);
+    const T dp = drelu_round1<T, N, F, CAP>((T)(x[0] + x[1]) & mask, nx2, g, mask, A.k_lo, A.s01, cap, A.n, A.begin + i, f, t);
 
     // preprocessing: [t], [s], [s][t]
     const StreamAt r012 = A.s012.at(g);
@@ -109,29 +113,29 @@ __device__ __forceinline__ void rss_element(const RssKArgs& A, const T* __restri
         const T gr[3] = {(T)(gb0 - gb2), (T)(gb1 - gb0), (T)(gb2 - gb1)};
         T z[3];
         rss_product<T>(x, y, gr, z);
-        st_nt(&Y0[e], (T)(z[0] & mask));
-        st_nt(&Y1[e], (T)(z[1] & mask));
-        st_nt(&Y2[e], (T)(z[2] & mask));
+        store_at(Y0, i, (T)(z[0] & mask));
+        store_at(Y1, i, (T)(z[1] & mask));
+        store_at(Y2, i, (T)(z[2] & mask));
     } else {
-        st_nt(&Y0[e], (T)(y[0] & mask));
-        st_nt(&Y1[e], (T)(y[1] & mask));
-        st_nt(&Y2[e], (T)(y[2] & mask));
+        store_at(Y0, i, (T)(y[0] & mask));
+        store_at(Y1, i, (T)(y[1] & mask));
+        store_at(Y2, i, (T)(y[2] & mask));
     }
 }
 
 // One call: grid-stride over the n elements of one share triple.
 template <typename T, int N, typename F, bool RELU, bool CAP>
 __device__ __forceinline__ void rss_loop(const RssKArgs& A, const F& f, T mask) {
-    const T* X0 = static_cast<const T*>(A.x0);
-    const T* X1 = static_cast<const T*>(A.x1);
-    const T* X2 = static_cast<const T*>(A.x2);
-    T* Y0 = static_cast<T*>(A.y0);
-    T* Y1 = static_cast<T*>(A.y1);
-    T* Y2 = static_cast<T*>(A.y2);
+    const T* X0 = static_cast<const T*>(A.x0) + A.begin;
+    const T* X1 = static_cast<const T*>(A.x1) + A.begin;
+    const T* X2 = static_cast<const T*>(A.x2) + A.begin;
+    T* Y0 = static_cast<T*>(A.y0) + A.begin;
+    T* Y1 = static_cast<T*>(A.y1) + A.begin;
+    T* Y2 = static_cast<T*>(A.y2) + A.begin;
     typename F::T* cap = static_cast<typename F::T*>(A.cap);
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t e = A.begin + (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < A.end; e += stride)
-        rss_element<T, N, F, RELU, CAP>(A, X0, X1, X2, Y0, Y1, Y2, cap, e, Index::of(A.elem_base + A.begin, e - A.begin), mask, f);
+    const uint32_t count = (uint32_t)(A.end - A.begin), stride = gridDim.x * blockDim.x;   // at most kLaunchElems
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < count; i += stride)
+        rss_element<T, N, F, RELU, CAP>(A, X0, X1, X2, Y0, Y1, Y2, cap, i, Index::of(A.elem_base + A.begin, i), mask, f);
 }
 
 // On a full-width ring the loop runs with the ring mask as a constant (see

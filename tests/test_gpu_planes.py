@@ -55,3 +55,26 @@ def test_walks_match_the_fused_call(B, setting, n):
 @pytest.mark.parametrize("setting", [(64, 18, 13), (64, 31, 0)])
 def test_planes_above_the_cache(B, setting, extra):
     check(B, setting, (1 << 22) + extra, (B.BC_OP_DRELU,))
+
+
+def test_calls_above_one_launch(B):
+    """A call of more than 2^28 elements runs as several launches; each continues the last one's elements."""
+    prm, sd = B.Params(32, 1, 3), B.Seeds(11, 12, 13, 14)
+    edge, n = 1 << 28, (1 << 28) + 77
+    x0, x1 = shares(B, prm, n, 5)
+    want = B.relu(x0, x1, prm, sd)
+    got = B.relu_pre(x0, x1, prm, B.rand_expand(B.BC_OP_RELU, prm, sd, n))
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    del got, want
+    want = B.drelu(x0, x1, prm, sd)
+    d0, d1 = B.drelu_reply(B.drelu_send(0, x0, prm, sd), B.drelu_send(1, x1, prm, sd), prm, sd)
+    assert torch.equal(B.drelu_finish(0, d0, prm, sd), want[0])
+    assert torch.equal(B.drelu_finish(1, d1, prm, sd), want[1])
+    del d0, d1, want
+    x2 = torch.zeros_like(x0)
+    sr = B.RssSeeds(11, 12, 13, 14, 15)
+    whole = B.rss_relu((x0, x1, x2), prm, sr)
+    cut = slice(edge - 50, n)
+    part = B.rss_relu(tuple(x[cut].clone() for x in (x0, x1, x2)), prm, sr, elem_base=edge - 50)
+    for a, b in zip(whole, part):
+        assert torch.equal(a[cut], b)

@@ -115,7 +115,7 @@ __host__ __device__ inline RandOffsets rand_offsets(uint32_t npos, bool relu, ui
 // start inside a 128-byte line, two waves share most lines, and around the L2
 // each line is two partial writes to memory.  Expansion, DReLU, us (around the
 // L2 in block order / through it by XCD), bytes an element in parentheses:
-//   N = 19 (116)  1,000,003 39 / 23   8,000,003 342 / 234   2^20 30 / 26   2^23 190 / 194
+//   N = 19 (124)  1,000,003 39 / 23   8,000,003 342 / 234   2^20 30 / 26   2^23 190 / 194
 //   N = 32 (288)  1,000,003 96 / 48   8,000,003 827 / 588   2^20 65 / 49   2^23 460 / 436
 //   N = 16 (80)   1,000,003 24 / 21   8,000,003 214 / 138   2^20 18.9 / 19.2
 // Up to 32 MB are then left in the L2s when the kernel ends, which costs small

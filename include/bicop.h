@@ -181,7 +181,7 @@ int bc_prg_blocks(uint32_t* out, uint64_t n, uint32_t nblocks, uint64_t seed,
  * the default prime) it writes out[i] = (a[i] b[i] + d[i]) mod p using the
  * same field code as the kernels: fp32-quotient products, Mersenne or
  * pseudo-Mersenne folds (with b and d shifted to the top of the word, as the
- * kernels keep their masks for the default prime at l_x = 16..20), fp64
+ * kernels keep their masks for the default prime at l_x = 16..30), fp64
  * quotient, Barrett or the 128-bit product.
  * Requires a[i], b[i] < p and d[i] <= p (other values give unspecified
  * results).  Device arrays of n uint64, 8-byte aligned. */

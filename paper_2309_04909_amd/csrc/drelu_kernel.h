@@ -166,7 +166,8 @@ __device__ __forceinline__ void slot_messages(uint32_t v0, uint32_t v1, typename
 // messages and their compares replaced by this test, the packed windows, the
 // grouped shuffle digits and window_sum (886 -> 725 instructions an element
 // at N = 19, 647 -> 463 for the N = 8 ReLU): DReLU at N = 19 and 2^24
-// elements 0.360 -> 0.298 ms, ReLU at N = 8 0.255 -> 0.209 ms; DReLU at
+// elements 0.360 -> 0.298 ms (0.285-0.288 at 691 instructions, with the scalar
+// Philox rounds and zero_high), ReLU at N = 8 0.255 -> 0.209 ms; DReLU at
 // N = 32 and 2^23 0.378 -> 0.277 ms, at N = 33 and 2^22 0.422 -> 0.231 ms.
 template <int N, typename F, int SH>
 struct SlotTest {

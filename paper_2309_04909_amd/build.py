@@ -67,7 +67,8 @@ def build(jobs: int | None = None, verbose: bool = False, asm: bool = False, ext
           build_dir: str = BUILD) -> str:
     """Compile every HIP source and link libbicop.so (or `out`).  Returns the library path."""
     os.makedirs(build_dir, exist_ok=True)
-    srcs = sources()
+    # the replicated-sharing and record instantiations compile longest: first
+    srcs = sorted(sources(), key=lambda s: not os.path.basename(s).startswith(("k_rss", "k_pre")))
     jobs = jobs or min(len(srcs), max(1, min(16, os.cpu_count() or 4)))
 
     def compile_one(src):

@@ -903,12 +903,11 @@ __global__ BC_KERNEL_ATTRS void k_drelu(DreluKArgs A, F f_arg) {
 // addresses (1,650 instructions an element and lane at N = 33 with two lanes,
 // against 1,286 here): DReLU at 65,536 elements, N = 33 9.8 -> 8.5 us, N = 19
 // 5.1 -> 4.5 us with two; 16,384 elements with four 6.4 -> 5.7 and 3.9 -> 3.7.
-template <int N, bool RELU, int G>
+template <int N, int FINISH, int G>
 struct WaveSlots {
-    // VALU instructions, roughly: a slot with its share of the mask blocks;
-    // role 0's draws and finish
+    // VALU instructions, roughly: a slot with its share of the mask blocks (and
+    // FINISH, role 0's draws and finish)
     static constexpr int SLOT = N <= 16 ? 24 : N <= 32 ? 19 + N / 2 : 58;
-    static constexpr int FINISH = RELU ? 165 : 45;
     static constexpr int first_count() {
         const int c = ((N * SLOT + FINISH) / G - FINISH + SLOT / 2) / SLOT;
         return c < 0 ? 0 : c;
@@ -919,11 +918,11 @@ struct WaveSlots {
 
 // Role ROLE's part of the element (in0, -n1): P2's minimum over its slots, and
 // the flip bit t.
-template <typename T, int N, typename F, bool RELU, int G, int ROLE>
+template <typename T, int N, typename F, int FINISH, int G, int ROLE>
 __device__ __forceinline__ uint32_t wave_slots(T in0, T n1, Index g, T mask, uint32_t k_lo, const Stream& s01, const F& f,
                                                uint32_t& t) {
     using FT = typename F::T;
-    using W = WaveSlots<N, RELU, G>;
+    using W = WaveSlots<N, FINISH, G>;
     using Test = SlotTest<N, F, MaskDraws<N, F>::SH>;
     constexpr int J0 = W::begin(ROLE), C = W::begin(ROLE + 1) - J0;
     const StreamAt r01 = s01.at(g);
@@ -962,14 +961,14 @@ __device__ __forceinline__ uint32_t wave_slots(T in0, T n1, Index g, T mask, uin
     return least;
 }
 
-template <typename T, int N, typename F, bool RELU, int G, int ROLE>
+template <typename T, int N, typename F, int FINISH, int G, int ROLE>
 __device__ __forceinline__ uint32_t wave_role(uint32_t role, T in0, T n1, Index g, T mask, uint32_t k_lo, const Stream& s01,
                                               const F& f, uint32_t& t) {
     if constexpr (ROLE == G - 1) {
-        return wave_slots<T, N, F, RELU, G, ROLE>(in0, n1, g, mask, k_lo, s01, f, t);
+        return wave_slots<T, N, F, FINISH, G, ROLE>(in0, n1, g, mask, k_lo, s01, f, t);
     } else {
-        if (role == ROLE) return wave_slots<T, N, F, RELU, G, ROLE>(in0, n1, g, mask, k_lo, s01, f, t);
-        return wave_role<T, N, F, RELU, G, ROLE + 1>(role, in0, n1, g, mask, k_lo, s01, f, t);
+        if (role == ROLE) return wave_slots<T, N, F, FINISH, G, ROLE>(in0, n1, g, mask, k_lo, s01, f, t);
+        return wave_role<T, N, F, FINISH, G, ROLE + 1>(role, in0, n1, g, mask, k_lo, s01, f, t);
     }
 }
 
@@ -997,7 +996,7 @@ __global__ BC_KERNEL_ATTRS void k_drelu_waves(DreluKArgs A, F f_arg) {
         T in0, n1;
         input_shares<T>(load_at(X0, e), load_at(X1, e), mask, (T)A.in_mask, A.k_in, in0, n1);
         uint32_t t;
-        uint32_t least = wave_role<T, N, F, RELU, G, 0>(role, in0, n1, g, mask, A.k_lo, A.s01, f, t);
+        uint32_t least = wave_role<T, N, F, (RELU ? 165 : 45), G, 0>(role, in0, n1, g, mask, A.k_lo, A.s01, f, t);
         if (role != 0) least_of[threadIdx.x] = least;
         T ba0 = 0, bb0 = 0, bc0 = 0, ba1 = 0, bb1 = 0, rho = 0;
         if (role == 0) {                                     // role 0's draws, before it waits

@@ -67,52 +67,52 @@ __device__ __forceinline__ T word_pair(uint32_t lo, uint32_t hi) {
     return (T)join64(lo, hi);
 }
 
-template <typename T, int N, typename F, bool RELU, bool CAP>
-__device__ __forceinline__ void rss_element(const RssKArgs& A, const T* __restrict__ X0, const T* __restrict__ X1,
-                                            const T* __restrict__ X2, T* Y0, T* Y1, T* Y2,
-                                            typename F::T* cap, uint32_t i, Index g, T mask, const F& f) {
-    const T x[3] = {load_at(X0, i), load_at(X1, i), load_at(X2, i)};
+// What the parties draw and form before P2 publishes D'': [s xor t] as q, s,
+// and the zero sharing of the ReLU's product.
+template <typename T, bool RELU>
+struct RssPrepared {
+    T q[3], gr[3], s;
+    __device__ __forceinline__ void prepare(const RssKArgs& A, Index g, uint32_t t) {
+        const StreamAt r012 = A.s012.at(g);
+        const Words4 b0 = r012.block(TAG_RSS, 0);
+        const Words4 b1 = r012.block(TAG_RSS, 1);
+        const Words4 b2 = r012.block(TAG_RSS, 2);
+        const Words4 b3 = r012.block(TAG_RSS, 3);
+        const Words4 c12 = A.s12.block(g, TAG_RSS, 0);
+        s = (T)(A.s2.block(g, TAG_RSS, 0).w0 & 1u);
+        const T al0 = word_pair<T>(b0.w0, b0.w1), al1 = word_pair<T>(b0.w2, b0.w3), al2 = word_pair<T>(b1.w0, b1.w1);
+        const T s1 = word_pair<T>(b1.w2, b1.w3), s2 = word_pair<T>(c12.w0, c12.w1);
+        const T ts[3] = {(T)(al0 - al2), (T)(al1 - al0 + (T)t), (T)(al2 - al1)};
+        const T ss[3] = {(T)(s - s1 - s2), s1, s2};
+        const T ga0 = word_pair<T>(b2.w0, b2.w1), ga1 = word_pair<T>(b2.w2, b2.w3), ga2 = word_pair<T>(b3.w0, b3.w1);
+        const T gst[3] = {(T)(ga0 - ga2), (T)(ga1 - ga0), (T)(ga2 - ga1)};
+        T st[3];
+        rss_product<T>(ss, ts, gst, st);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) q[j] = (T)(ss[j] + ts[j] - (T)2 * st[j]);   // [s xor t]_j
+        if constexpr (RELU) {
+            const Words4 b4 = r012.block(TAG_RSS, 4);
+            const T gb0 = word_pair<T>(b3.w2, b3.w3), gb1 = word_pair<T>(b4.w0, b4.w1), gb2 = word_pair<T>(b4.w2, b4.w3);
+            gr[0] = (T)(gb0 - gb2);
+            gr[1] = (T)(gb1 - gb0);
+            gr[2] = (T)(gb2 - gb1);
+        }
+    }
+};
 
-    // round 1 and P2's zero test on the 2-of-2 input ([x]_0 + [x]_1, [x]_2),
-    // whose second holder cuts its negated share -[x]_2
-    uint32_t t;
-    const T nx2 = (T)((T)0 - x[2]) & mask;
-    const T dp = drelu_round1<T, N, F, CAP>((T)(x[0] + x[1]) & mask, nx2, g, mask, A.k_lo, A.s01, cap, A.n, A.begin + i, f, t);
-
-    // preprocessing: [t], [s], [s][t]
-    const StreamAt r012 = A.s012.at(g);
-    const Words4 b0 = r012.block(TAG_RSS, 0);
-    const Words4 b1 = r012.block(TAG_RSS, 1);
-    const Words4 b2 = r012.block(TAG_RSS, 2);
-    const Words4 b3 = r012.block(TAG_RSS, 3);
-    const Words4 c12 = A.s12.block(g, TAG_RSS, 0);
-    const T s = (T)(A.s2.block(g, TAG_RSS, 0).w0 & 1u);
-    const T al0 = word_pair<T>(b0.w0, b0.w1), al1 = word_pair<T>(b0.w2, b0.w3), al2 = word_pair<T>(b1.w0, b1.w1);
-    const T s1 = word_pair<T>(b1.w2, b1.w3), s2 = word_pair<T>(c12.w0, c12.w1);
-    const T ts[3] = {(T)(al0 - al2), (T)(al1 - al0 + (T)t), (T)(al2 - al1)};
-    const T ss[3] = {(T)(s - s1 - s2), s1, s2};
-    const T ga0 = word_pair<T>(b2.w0, b2.w1), ga1 = word_pair<T>(b2.w2, b2.w3), ga2 = word_pair<T>(b3.w0, b3.w1);
-    const T gst[3] = {(T)(ga0 - ga2), (T)(ga1 - ga0), (T)(ga2 - ga1)};
-    T st[3];
-    rss_product<T>(ss, ts, gst, st);
-
-    // P2's public reply and the finish: y_j = q_j - 2 D'' q_j (+ D'' on share 0)
-    // (the sign as xor and add: a select per word costs what both do, and the
-    // add of D'' on share 0 is the negation's own + 1)
-    const T dpp = dp ^ s, neg = (T)((T)0 - dpp);
+// P2's public reply and the finish: y_j = q_j - 2 D'' q_j (+ D'' on share 0)
+// (the sign as xor and add: a select per word costs what both do, and the add
+// of D'' on share 0 is the negation's own + 1), and the ReLU's product.
+template <typename T, bool RELU>
+__device__ __forceinline__ void rss_finish(T dp, const T (&x)[3], const RssPrepared<T, RELU>& P, T* Y0, T* Y1, T* Y2,
+                                           uint32_t i, T mask) {
+    const T dpp = dp ^ P.s, neg = (T)((T)0 - dpp);
     T y[3];
 #pragma unroll
-    for (int j = 0; j < 3; ++j) {
-        const T q = (T)(ss[j] + ts[j] - (T)2 * st[j]);               // [s xor t]_j
-        y[j] = (T)((q ^ neg) + (j == 0 ? (T)(2 * dpp) : dpp));
-    }
-
+    for (int j = 0; j < 3; ++j) y[j] = (T)((P.q[j] ^ neg) + (j == 0 ? (T)(2 * dpp) : dpp));
     if constexpr (RELU) {
-        const Words4 b4 = r012.block(TAG_RSS, 4);
-        const T gb0 = word_pair<T>(b3.w2, b3.w3), gb1 = word_pair<T>(b4.w0, b4.w1), gb2 = word_pair<T>(b4.w2, b4.w3);
-        const T gr[3] = {(T)(gb0 - gb2), (T)(gb1 - gb0), (T)(gb2 - gb1)};
         T z[3];
-        rss_product<T>(x, y, gr, z);
+        rss_product<T>(x, y, P.gr, z);
         store_at(Y0, i, (T)(z[0] & mask));
         store_at(Y1, i, (T)(z[1] & mask));
         store_at(Y2, i, (T)(z[2] & mask));
@@ -121,6 +121,21 @@ __device__ __forceinline__ void rss_element(const RssKArgs& A, const T* __restri
         store_at(Y1, i, (T)(y[1] & mask));
         store_at(Y2, i, (T)(y[2] & mask));
     }
+}
+
+// Element i of a launch.  Round 1 and P2's zero test run on the 2-of-2 input
+// ([x]_0 + [x]_1, [x]_2), whose second holder cuts its negated share -[x]_2.
+template <typename T, int N, typename F, bool RELU, bool CAP>
+__device__ __forceinline__ void rss_element(const RssKArgs& A, const T* __restrict__ X0, const T* __restrict__ X1,
+                                            const T* __restrict__ X2, T* Y0, T* Y1, T* Y2,
+                                            typename F::T* cap, uint32_t i, Index g, T mask, const F& f) {
+    const T x[3] = {load_at(X0, i), load_at(X1, i), load_at(X2, i)};
+    uint32_t t;
+    const T nx2 = (T)((T)0 - x[2]) & mask;
+    const T dp = drelu_round1<T, N, F, CAP>((T)(x[0] + x[1]) & mask, nx2, g, mask, A.k_lo, A.s01, cap, A.n, A.begin + i, f, t);
+    RssPrepared<T, RELU> P;
+    P.prepare(A, g, t);
+    rss_finish<T, RELU>(dp, x, P, Y0, Y1, Y2, i, mask);
 }
 
 // One call: grid-stride over the n elements of one share triple.
@@ -152,6 +167,54 @@ __global__ BC_KERNEL_ATTRS void k_rss(RssKArgs A, F f_arg) {
     rss_loop<T, N, F, RELU, CAP>(A, f, in_vgpr((T)A.ring_mask));
 }
 
+// Small calls: G waves share 64 elements as in k_drelu_waves, whose roles and
+// slots these are; role 0 prepares the sharings and finishes, and so takes few
+// or none of the slots.  Such calls are bound by one wave's issue rate, one
+// VALU instruction per 8.4 cycles; the rule (lanes_per_element) is that of
+// the 2-of-2 calls.  A call, us at G = 1 / 2 / 4: l_x = 18 ReLU 1,024 elements
+// 5.8 / 4.9 / 4.0, 32,768 6.5 / 5.4 / 4.7, 65,536 6.1 / 5.9 / 5.4, 131,072
+// 7.4 / 7.5 / 8.8; l_x = 7 DReLU 16,384 4.5 / 3.6 / 3.5, 65,536 4.6 / 4.0 / 4.3;
+// l_x = 32 ReLU 16,384 11.0 / 8.2 / 6.3, 65,536 11.1 / 9.9 / 11.5.
+template <typename T, int N, typename F, bool RELU, int G>
+__global__ BC_KERNEL_ATTRS void k_rss_waves(RssKArgs A, F f_arg) {
+    static_assert(G == 2 || G == 4, "G: waves of a 256-thread block that share elements");
+    constexpr uint32_t EPB = 256 / G;
+    constexpr int FINISH = RELU ? 343 : 250;                 // VALU instructions, roughly
+    __shared__ uint32_t least_of[256];
+    const F f = f_arg.vgpr();
+    const T* X0 = static_cast<const T*>(A.x0) + A.begin;
+    const T* X1 = static_cast<const T*>(A.x1) + A.begin;
+    const T* X2 = static_cast<const T*>(A.x2) + A.begin;
+    T* Y0 = static_cast<T*>(A.y0) + A.begin;
+    T* Y1 = static_cast<T*>(A.y1) + A.begin;
+    T* Y2 = static_cast<T*>(A.y2) + A.begin;
+    const T mask = in_vgpr((T)A.ring_mask);
+    const uint32_t n = (uint32_t)(A.end - A.begin);          // at most kLaunchElems
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), role = wave % G;
+    for (uint32_t b = blockIdx.x * EPB; b < n; b += gridDim.x * EPB) {
+        const uint32_t want = b + (wave / G) * 64 + (threadIdx.x & 63u);
+        const uint32_t i = want < n ? want : n - 1;
+        const Index g = Index::of(A.elem_base + A.begin, i);
+        const T x[3] = {load_at(X0, i), load_at(X1, i), load_at(X2, i)};
+        const T nx2 = (T)((T)0 - x[2]) & mask;
+        uint32_t t;
+        uint32_t least = wave_role<T, N, F, FINISH, G, 0>(role, (T)(x[0] + x[1]) & mask, nx2, g, mask, A.k_lo, A.s01, f, t);
+        RssPrepared<T, RELU> P;
+        if (role != 0)
+            least_of[threadIdx.x] = least;
+        else
+            P.prepare(A, g, t);
+        __syncthreads();
+        if (role == 0) {
+#pragma unroll
+            for (int r = 1; r < G; ++r) least = min(least, least_of[threadIdx.x + 64 * r]);
+            const T dp = least <= SlotTest<N, F, MaskDraws<N, F>::SH>::LIMIT ? 1 : 0;
+            if (want < n) rss_finish<T, RELU>(dp, x, P, Y0, Y1, Y2, i, mask);
+        }
+        __syncthreads();                                     // role 0 has read before the next elements' minima
+    }
+}
+
 inline Stream stream_of(const StreamKey& k) { return Stream{k.k0, k.k1, k.n0, k.n1}; }
 
 template <typename T, int N, bool RELU>
@@ -177,6 +240,16 @@ hipError_t launch_rss_exact(const RssLaunch& L, hipStream_t st) {
         return by_index_range(L.elem_base, L.n, [&](uint64_t begin, uint64_t end) {
             A.begin = begin;
             A.end = end;
+            if constexpr (F::kDefault) {                     // other primes: one lane per element
+                if (L.group == 4) {
+                    hipLaunchKernelGGL((k_rss_waves<T, N, F, RELU, 4>), dim3(L.grid), dim3(256), 0, st, A, f);
+                    return;
+                }
+                if (L.group == 2) {
+                    hipLaunchKernelGGL((k_rss_waves<T, N, F, RELU, 2>), dim3(L.grid), dim3(256), 0, st, A, f);
+                    return;
+                }
+            }
             if (L.cap)
                 hipLaunchKernelGGL((k_rss<T, N, F, RELU, true>), dim3(L.grid), dim3(256), 0, st, A, f);
             else

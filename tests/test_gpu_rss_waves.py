@@ -1,0 +1,32 @@
+"""Small replicated-sharing calls split an element's slots over 2 or 4 waves.
+They must give exactly the one-lane kernel's shares (integers: no tolerance);
+the capturing call always runs one lane per element.  Sizes: one lane, the
+edges of a wave and of a block, both sides of the limits of 4 and of 2 waves."""
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("op", ["rss_drelu", "rss_relu"])
+@pytest.mark.parametrize("ell,lx,k_lo", [(64, 1, 3), (64, 7, 11), (51, 11, 13), (64, 18, 13), (64, 31, 0), (64, 32, 0),
+                                         (32, 8, 8), (24, 7, 10)])
+def test_waves_equal_one_lane(ell, lx, k_lo, op):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2309_04909_amd import bicop as B
+    prm, seeds = B.Params(ell, lx, k_lo), B.RssSeeds(21, 22, 23, 24, 25, 26)
+    gen = torch.Generator(device="cuda").manual_seed(lx)
+    bound = 1 << (k_lo + lx - 1)
+    for n in (1, 63, 64, 65, 4097, 32768, 32769, 65536, 65537):
+        x = torch.randint(-bound + 1, bound, (n,), generator=gen, device="cuda", dtype=torch.int64)
+        r = [torch.randint(-(1 << 62), 1 << 62, (n,), generator=gen, device="cuda", dtype=torch.int64) for _ in range(2)]
+        s = [x - r[0] - r[1], r[0], r[1]]
+        if ell < 64:
+            s = [v & ((1 << ell) - 1) for v in s]
+        s = tuple(v.to(B.ring_dtype(ell)) for v in s)
+        got = getattr(B, op)(s, prm, seeds, elem_base=(1 << 32) - 40)
+        want, _ = getattr(B, op)(s, prm, seeds, elem_base=(1 << 32) - 40, capture=True)
+        for a, b in zip(got, want):
+            assert torch.equal(a, b), n

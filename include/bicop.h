@@ -196,11 +196,13 @@ int bc_zp_mul_add(const uint64_t* a, const uint64_t* b, const uint64_t* d, uint6
 #define BC_SCHED_PRE     2u   /* bc_drelu_pre, bc_relu_pre               */
 #define BC_SCHED_EXPAND  3u   /* bc_rand_expand                          */
 #define BC_SCHED_BATCH   4u   /* bc_batch_run with grid = 0              */
-#define BC_SCHED_GROUP   5u   /* bc_drelu, bc_relu on small n: the value is
+#define BC_SCHED_GROUP   5u   /* bc_drelu, bc_relu, bc_rss_drelu and
+                                 bc_rss_relu on small n: the value is
                                  the largest number of lanes per element
                                  (1 = off, 2, 4 or more for up to 4; default
-                                 8)                                        */
-#define BC_SCHED_GROUP_FILL 6u /* bc_drelu, bc_relu: several lanes per element
+                                 8); the replicated-sharing calls take 4
+                                 where it gives more than 1               */
+#define BC_SCHED_GROUP_FILL 6u /* the same calls: several lanes per element
                                  are used while n times the lanes stays
                                  within this many waves per SIMD (default 2) */
 

@@ -342,8 +342,9 @@ int rss_common(bool relu, const void* x0, const void* x1, const void* x2, void* 
     L.s12 = stream_key(seeds->seed12, seeds->nonce);
     L.s012 = stream_key(seeds->seed012, seeds->nonce);
     L.s2 = stream_key(seeds->seed2, seeds->nonce);
-    L.group = lanes_per_element(L.npos, w, relu, n, capture != nullptr);
-    L.grid = (int)sched_grid(BC_SCHED_FUSED, L.npos, w, relu, (n * (uint64_t)L.group + 255) / 256);
+    const int lanes = lanes_per_element(L.npos, w, relu, n, capture != nullptr);
+    L.waves = lanes == 4 || (lanes == 2 && L.npos <= 32);
+    L.grid = (int)sched_grid(BC_SCHED_FUSED, L.npos, w, relu, (n * (L.waves ? 4u : 1u) + 255) / 256);
     hipStream_t st = (hipStream_t)stream;
     hipError_t e;
     if (r.ell > 32)

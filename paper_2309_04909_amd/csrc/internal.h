@@ -145,7 +145,8 @@ struct RssLaunch {
     uint32_t ell, lx, k_lo, npos;
     bool relu;
     StreamKey s01, s12, s012, s2;
-    int grid, group;          // group: waves that share an element's slots (k_rss_waves), 1, 2 or 4
+    int grid;
+    bool waves;               // four waves share an element's slots (k_rss_waves)
 };
 
 hipError_t launch_rss_u64_lo(const RssLaunch& L, hipStream_t st);    // N 2..12

@@ -167,17 +167,19 @@ __global__ BC_KERNEL_ATTRS void k_rss(RssKArgs A, F f_arg) {
     rss_loop<T, N, F, RELU, CAP>(A, f, in_vgpr((T)A.ring_mask));
 }
 
-// Small calls: G waves share 64 elements as in k_drelu_waves, whose roles and
-// slots these are; role 0 prepares the sharings and finishes, and so takes few
-// or none of the slots.  Such calls are bound by one wave's issue rate, one
-// VALU instruction per 8.4 cycles; the rule (lanes_per_element) is that of
-// the 2-of-2 calls.  A call, us at G = 1 / 2 / 4: l_x = 18 ReLU 1,024 elements
-// 5.8 / 4.9 / 4.0, 32,768 6.5 / 5.4 / 4.7, 65,536 6.1 / 5.9 / 5.4, 131,072
-// 7.4 / 7.5 / 8.8; l_x = 7 DReLU 16,384 4.5 / 3.6 / 3.5, 65,536 4.6 / 4.0 / 4.3;
-// l_x = 32 ReLU 16,384 11.0 / 8.2 / 6.3, 65,536 11.1 / 9.9 / 11.5.
-template <typename T, int N, typename F, bool RELU, int G>
+// Small calls: the four waves of a block share 64 elements as in
+// k_drelu_waves, whose roles and slots these are; role 0 prepares the sharings
+// and finishes, and so takes few or none of the slots.  Such calls are bound
+// by one wave's issue rate, one VALU instruction per 8.4 cycles.  A call, us
+// at one lane / two waves / four waves: l_x = 18 ReLU 1,024 elements 5.8 / 4.9
+// / 4.0, 32,768 6.5 / 5.4 / 4.7, 65,536 6.1 / 5.9 / 5.4, 131,072 7.4 / 7.5 /
+// 8.8; l_x = 7 DReLU 16,384 4.5 / 3.6 / 3.5, 65,536 4.6 / 4.0 / 4.3; l_x = 32
+// ReLU 16,384 11.0 / 8.2 / 6.3, 65,536 11.1 / 9.9 / 11.5.  So four waves run
+// wherever the 2-of-2 call takes more than one lane, at l_x = 32 only where it
+// takes four.
+template <typename T, int N, typename F, bool RELU>
 __global__ BC_KERNEL_ATTRS void k_rss_waves(RssKArgs A, F f_arg) {
-    static_assert(G == 2 || G == 4, "G: waves of a 256-thread block that share elements");
+    constexpr int G = 4;
     constexpr uint32_t EPB = 256 / G;
     constexpr int FINISH = RELU ? 343 : 250;                 // VALU instructions, roughly
     __shared__ uint32_t least_of[256];
@@ -241,12 +243,8 @@ hipError_t launch_rss_exact(const RssLaunch& L, hipStream_t st) {
             A.begin = begin;
             A.end = end;
             if constexpr (F::kDefault) {                     // other primes: one lane per element
-                if (L.group == 4) {
-                    hipLaunchKernelGGL((k_rss_waves<T, N, F, RELU, 4>), dim3(L.grid), dim3(256), 0, st, A, f);
-                    return;
-                }
-                if (L.group == 2) {
-                    hipLaunchKernelGGL((k_rss_waves<T, N, F, RELU, 2>), dim3(L.grid), dim3(256), 0, st, A, f);
+                if (L.waves) {
+                    hipLaunchKernelGGL((k_rss_waves<T, N, F, RELU>), dim3(L.grid), dim3(256), 0, st, A, f);
                     return;
                 }
             }

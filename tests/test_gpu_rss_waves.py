@@ -1,7 +1,7 @@
-"""Small replicated-sharing calls split an element's slots over 2 or 4 waves.
+"""Small replicated-sharing calls split an element's slots over 4 waves.
 They must give exactly the one-lane kernel's shares (integers: no tolerance);
 the capturing call always runs one lane per element.  Sizes: one lane, the
-edges of a wave and of a block, both sides of the limits of 4 and of 2 waves."""
+edges of a wave and of a block, both sides of the limits."""
 
 import pytest
 

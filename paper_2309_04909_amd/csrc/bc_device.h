@@ -86,14 +86,21 @@ __device__ __forceinline__ void st_plane(P* p, P v) {
 }
 
 // The planes [0, 1, ...][n] from p, in turn.  The step is opaque, so that a
-// loop over the elements keeps one pointer and not one per plane (which do
-// not fit the scalar registers).
+// loop over the elements keeps one pointer in scalar registers and not one per
+// plane (which do not fit them).  The pointer is one of the global address
+// space: behind the asm the compiler could no longer tell that a generic one
+// is, and every plane after the first would be a FLAT access, with its own
+// 64-bit address in vector registers and counted with the LDS accesses (N = 19:
+// 16 FLAT stores of 18 in the expansion, 540 VALU instructions instead of 522;
+// 32 FLAT loads of 42 in the online call, 1,002 instead of 966).
 template <typename P>
 struct Planes {
-    P* at;
+    typedef __attribute__((address_space(1))) P GlobalP;
+    GlobalP* at;
     uint64_t n;
+    __device__ __forceinline__ Planes(P* p, uint64_t n_) : at((GlobalP*)p), n(n_) {}
     __device__ __forceinline__ P* next() {
-        P* p = at;
+        P* p = (P*)at;
         at += n;
         asm("" : "+s"(at));
         return p;

@@ -107,17 +107,33 @@ struct Planes {
     }
 };
 
-// The calling block's place in the walk over the elements: blockIdx, or with
-// BY_XCD an order in which the blocks of one XCD are neighbours (the hardware
-// deals blockIdx out to the 8 XCDs in turn), so that one L2 merges their
-// stores to a shared line.
-template <bool BY_XCD>
-__device__ __forceinline__ uint32_t walk_block() {
-    const uint32_t b = blockIdx.x;
-    if constexpr (!BY_XCD) return b;
-    const uint32_t x = b & 7u, per = gridDim.x >> 3, rest = gridDim.x & 7u;
-    return x * per + (x < rest ? x : rest) + (b >> 3);
+// What one thread of a grid's walk over the elements takes: begin, begin +
+// stride, ... below end.
+struct WalkRange {
+    uint32_t begin, end, stride;
+};
+
+// The part of thread t of block b in the walk of `grid` blocks of 256 threads
+// over count elements (at most kLaunchElems), in block order or by XCD (a grid
+// of walk_grid's blocks).  The hardware deals blocks out to the 8 XCDs in turn
+// (b mod 8 is block b's XCD), and by XCD each of them walks an eighth of the
+// elements, consecutive ones, so that one L2 merges the stores to a shared
+// line.  The eighths are fixed by the elements, not by the grid: blocks that
+// are only renumbered by XCD and stride over the whole range leave the last,
+// partial stride to the first XCDs (5,000,001 elements on 16,384 blocks: the
+// first XCD took two elements a thread, most others one; an N = 19 send 127 us
+// so, 89 in block order and 80 by eighths).
+__host__ __device__ constexpr WalkRange walk_range(bool by_xcd, uint32_t b, uint32_t t, uint32_t grid, uint32_t count) {
+    if (!by_xcd) return WalkRange{b * 256 + t, count, grid * 256};
+    const uint32_t x = b & 7u, chunks = (count + 255) / 256;
+    const uint32_t c0 = chunks * x >> 3, c1 = chunks * (x + 1) >> 3;
+    return WalkRange{(c0 + (b >> 3)) * 256 + t, c1 * 256 < count ? c1 * 256 : count, (grid >> 3) * 256};
 }
+template <bool BY_XCD>
+__device__ __forceinline__ WalkRange walk_range(uint32_t count) {
+    return walk_range(BY_XCD, blockIdx.x, threadIdx.x, gridDim.x, count);
+}
+inline uint32_t walk_grid(bool by_xcd, uint32_t grid) { return by_xcd ? (grid + 7) / 8 * 8 : grid; }
 
 constexpr uint32_t TAG_SHUFFLE = 1;
 constexpr uint32_t TAG_MASK = 2;

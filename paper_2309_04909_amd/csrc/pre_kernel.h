@@ -81,8 +81,8 @@ template <typename T, int N, typename F, bool RELU, bool NT>
 __global__ BC_KERNEL_ATTRS void k_expand(ExpandKArgs A, F f) {
     const T mask = (T)A.ring_mask;
     const uint64_t n = A.n;
-    const uint32_t count = (uint32_t)(A.end - A.begin), stride = gridDim.x * blockDim.x;   // at most kLaunchElems
-    for (uint32_t i = walk_block<!NT>() * blockDim.x + threadIdx.x; i < count; i += stride) {
+    const WalkRange W = walk_range<!NT>((uint32_t)(A.end - A.begin));
+    for (uint32_t i = W.begin; i < W.end; i += W.stride) {
         const Index g = Index::of(A.elem_base + A.begin, i);
         const StreamAt r01 = A.s01.at(g);
         Planes<uint32_t> perms{A.perm + A.begin, n};
@@ -222,8 +222,8 @@ __device__ __forceinline__ void drelu_pre_loop(const PreKArgs& A, const F& f, T 
     typename F::T* cap = static_cast<typename F::T*>(A.cap);
     if constexpr (CAP) cap += A.begin * N;
     const RecordView<T> R = RecordView<T>{A.perm, static_cast<const uint64_t*>(A.rz), static_cast<const T*>(A.tail), A.n}.from(A.begin);
-    const uint32_t count = (uint32_t)(A.end - A.begin), stride = gridDim.x * blockDim.x;   // at most kLaunchElems
-    for (uint32_t i = walk_block<!NT>() * blockDim.x + threadIdx.x; i < count; i += stride)
+    const WalkRange W = walk_range<!NT>((uint32_t)(A.end - A.begin));
+    for (uint32_t i = W.begin; i < W.end; i += W.stride)
         drelu_pre_element<T, N, F, RELU, CAP, NT>(X0, X1, Y0, Y1, cap, R, i, Index::of(A.elem_base + A.begin, i), mask, mask, 0, A.k_lo,
                                               A.s02, A.s12, f);
 }
@@ -247,7 +247,7 @@ hipError_t launch_expand(const PreLaunch& L, ExpandKArgs A, const F& f, hipStrea
     return by_index_range(L.elem_base, L.n, [&](uint64_t begin, uint64_t end) {
         A.begin = begin;
         A.end = end;
-        hipLaunchKernelGGL((k_expand<T, N, F, RELU, NT>), dim3(L.grid), dim3(256), 0, st, A, f);
+        hipLaunchKernelGGL((k_expand<T, N, F, RELU, NT>), dim3(walk_grid(!NT, L.grid)), dim3(256), 0, st, A, f);
     });
 }
 
@@ -256,7 +256,7 @@ hipError_t launch_pre(const PreLaunch& L, PreKArgs A, const F& f, hipStream_t st
     return by_index_range(L.elem_base, L.n, [&](uint64_t begin, uint64_t end) {
         A.begin = begin;
         A.end = end;
-        hipLaunchKernelGGL((k_drelu_pre<T, N, F, RELU, CAP, NT>), dim3(L.grid), dim3(256), 0, st, A, f);
+        hipLaunchKernelGGL((k_drelu_pre<T, N, F, RELU, CAP, NT>), dim3(walk_grid(!NT, L.grid)), dim3(256), 0, st, A, f);
     });
 }
 

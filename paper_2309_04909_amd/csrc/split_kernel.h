@@ -78,8 +78,8 @@ __global__ BC_KERNEL_ATTRS void k_send(SplitKArgs A, F f_arg) {
     const T* X = static_cast<const T*>(A.in0);
     uint32_t* M = static_cast<uint32_t*>(A.out0);
     const T mask = in_vgpr((T)A.ring_mask);
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t e = A.begin + (uint64_t)walk_block<true>() * blockDim.x + threadIdx.x; e < A.end; e += stride) {
+    const WalkRange R = walk_range<true>((uint32_t)(A.end - A.begin));
+    for (uint64_t e = A.begin + R.begin; e < A.begin + R.end; e += R.stride) {
         const Index g = Index::of(A.elem_base + A.begin, e - A.begin);
         const T x = X[e] & mask;
         const StreamAt r01 = A.s01.at(g);
@@ -113,8 +113,8 @@ __global__ BC_KERNEL_ATTRS void k_reply(SplitKArgs A, F f_arg) {
     T* D0 = static_cast<T*>(A.out0);
     T* D1 = static_cast<T*>(A.out1);
     const T mask = in_vgpr((T)A.ring_mask);
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t e = A.begin + (uint64_t)walk_block<!NT>() * blockDim.x + threadIdx.x; e < A.end; e += stride) {
+    const WalkRange R = walk_range<!NT>((uint32_t)(A.end - A.begin));
+    for (uint64_t e = A.begin + R.begin; e < A.begin + R.end; e += R.stride) {
         uint32_t w0[W], w1[W];
 #pragma unroll
         for (int k = 0; k < W; ++k) {
@@ -173,9 +173,9 @@ hipError_t launch_send(const SplitLaunch& L, SplitKArgs A, const F& f, hipStream
         A.begin = begin;
         A.end = end;
         if (L.party == 0)
-            hipLaunchKernelGGL((k_send<T, N, F, 0>), dim3(L.grid), dim3(256), 0, st, A, f);
+            hipLaunchKernelGGL((k_send<T, N, F, 0>), dim3(walk_grid(true, L.grid)), dim3(256), 0, st, A, f);
         else
-            hipLaunchKernelGGL((k_send<T, N, F, 1>), dim3(L.grid), dim3(256), 0, st, A, f);
+            hipLaunchKernelGGL((k_send<T, N, F, 1>), dim3(walk_grid(true, L.grid)), dim3(256), 0, st, A, f);
     });
 }
 
@@ -184,7 +184,7 @@ hipError_t launch_reply(const SplitLaunch& L, SplitKArgs A, const F& f, hipStrea
     return by_index_range(L.elem_base, L.n, [&](uint64_t begin, uint64_t end) {
         A.begin = begin;
         A.end = end;
-        hipLaunchKernelGGL((k_reply<T, N, F, NT>), dim3(L.grid), dim3(256), 0, st, A, f);
+        hipLaunchKernelGGL((k_reply<T, N, F, NT>), dim3(walk_grid(!NT, L.grid)), dim3(256), 0, st, A, f);
     });
 }
 

@@ -388,8 +388,19 @@ int split_common(bc::SplitLaunch::Kind kind, uint32_t party, const void* in0, co
     L.npos = r.lx + 1;
     L.s01 = stream_key(seeds->seed01, seeds->nonce);
     L.s02 = stream_key(seeds->seed02, seeds->nonce);
+    uint64_t work = (n + 255) / 256;
+    if (kind == bc::SplitLaunch::FINISH) {
+        // The unflip is a streaming call with a generator block an element: a
+        // thread that takes several has the next one's share in flight while
+        // it computes, so its grid stays below the streaming calls' own.  Us at
+        // 16 / 64 / 1024 blocks a unit, l = 64: 9,000,001 elements 23 / 21.8 /
+        // 22.8, 2^24 41 / 39 / 42.7; l = 32 (8 / 64 / 1024): 4,000,003 8.1 / 8.5 /
+        // 8.5, 2^24 27.7 / 24.4 / 30.2, 2^26 118 / 141 / 165.
+        const uint64_t most = (uint64_t)grid_cap(w == 8 ? 64 : 8);
+        if (work > most) work = most;
+    }
     L.grid = (int)sched_grid(kind == bc::SplitLaunch::FINISH ? BC_SCHED_STREAM : BC_SCHED_FUSED,
-                             kind == bc::SplitLaunch::FINISH ? 0 : L.npos, w, false, (n + 255) / 256);
+                             kind == bc::SplitLaunch::FINISH ? 0 : L.npos, w, false, work);
     hipStream_t st = (hipStream_t)stream;
     hipError_t e;
     if (kind == bc::SplitLaunch::FINISH)

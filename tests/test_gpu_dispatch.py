@@ -1,0 +1,28 @@
+"""Which kernel and grid a call takes, read from a captured graph: results do
+not show a dispatch that went wrong."""
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def B():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2309_04909_amd import bicop
+    return bicop
+
+
+@pytest.mark.parametrize("ell,lx,per_unit", [(64, 18, 64), (32, 8, 8)])
+def test_finish_grid(B, ell, lx, per_unit):
+    """P0's and P1's unflip strides above 64 (8-byte shares) or 8 blocks a compute unit."""
+    from graph_kernels import kernels
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    prm, sd = B.Params(ell, lx, 8), B.Seeds(1, 2, 3, 4)
+    for n in (1, 256 * units * per_unit - 1, 256 * units * per_unit, 256 * units * per_unit + 1, 4 * 256 * units * per_unit):
+        d = torch.zeros(n, dtype=torch.int64 if ell > 32 else torch.int32, device="cuda")
+        for party in (0, 1):
+            (name, blocks), = kernels(lambda: B.drelu_finish(party, d, prm, sd, out=d))
+            assert "k_finish" in name and blocks == min((n + 255) // 256, units * per_unit), n

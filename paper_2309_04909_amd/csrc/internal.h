@@ -108,29 +108,56 @@ __host__ __device__ inline RandOffsets rand_offsets(uint32_t npos, bool relu, ui
     return o;
 }
 
-// How planes (the word-major arrays [planes][n] of a record or of packed
-// messages, `bytes` of them an element) are written and read.
+// How planes (the word-major arrays [planes][n] of a record, or of both packed
+// messages) are written and read: `first` is the first of them, `bytes` what
+// all of them hold an element.
 //
-// Written through the L2, by XCD: where n is no multiple of 32 the planes
-// start inside a 128-byte line, two waves share most lines, and around the L2
-// each line is two partial writes to memory.  Expansion, DReLU, us (around the
-// L2 in block order / through it by XCD), bytes an element in parentheses:
-//   N = 19 (124)  1,000,003 39 / 23   8,000,003 342 / 234   2^20 30 / 26   2^23 190 / 194
-//   N = 32 (288)  1,000,003 96 / 48   8,000,003 827 / 588   2^20 65 / 49   2^23 460 / 436
-//   N = 16 (80)   1,000,003 24 / 21   8,000,003 214 / 138   2^20 18.9 / 19.2
-// Up to 32 MB are then left in the L2s when the kernel ends, which costs small
-// records (bound by the VALU) more than it gives: N = 8 ReLU (32) 1,000,003
-// 14.6 / 16.7, 3,211,264 37 / 38.  Messages are read at once by the reply
-// (send + send + reply + finish, N = 19, 1,000,003: 77 / 73).
-constexpr bool planes_around_l2(uint64_t bytes) { return bytes < 48; }
+// Written around the L2 in block order, or through it by XCD.  Where n is no
+// multiple of 32 (or `first` is off a line) the planes start inside a 128-byte
+// line: two waves share most lines, and around the L2 each line is two partial
+// writes to memory.  Through the L2 up to 32 MB are left in it when the kernel
+// ends, to be written back before the next one starts, which costs small planes
+// more than shared lines do (two messages leave twice as much).  A writer and
+// its reader in turn (expansion and online call; both sends, the reply and both
+// finishes), around / through the L2 with the better one as 1, MiB of planes
+// before the colon:
+//   shared lines  records   N = 10, 262,145, 11: 1 / 1.03       N = 24, 131,073, 27: 1.07 / 1
+//                           N = 19, 1,000,003, 125: 1.31 / 1    N = 19, 5,000,001, 629: 1.42 / 1
+//                 messages  N = 28, 65,537, 12: 1 / 1.06        N = 16, 262,145, 16: 1 / 1.02
+//                           N = 12, 524,289, 20: 1.03 / 1       N = 24, 524,289, 72: 1.07 / 1
+//   whole lines   messages  N = 19, 2^17, 12: 1 / 1.13          N = 21, 2^19, 56: 1 / 1.01
+//                           N = 32, 2^19, 128: 1.01 / 1         N = 32, 2^22, 1,024: 1 / 1.06
+//                 records   N = 14, 2^19, 36: 1 / 1.11          N = 24, 2^18, 54: 1 / 1.07
+//                           N = 17, 2^19, 62: 1.03 / 1          N = 16, 2^20, 80: 1.05 / 1
+//                           N = 32, 2^20, 288: 1.22 / 1         N = 32, 2^21, 576: 1.10 / 1
+//                           N = 19, 3,211,264, 404: 1.04 / 1    N = 19, 6,422,528, 808: 1 / 1.03
+// Records are also expanded ahead of time.  That alone is slower through the L2
+// from between 2^21 and 3 2^20 elements on (N = 19 ReLU, us: 2^20 30 / 28, 3,211,264
+// 69 / 83, 2^23 173 / 211; N = 17: 2^21 52 / 47, 3,211,264 67 / 77), which the
+// sequence above does not make up for.
+constexpr uint64_t kMiB = 1ull << 20;
+constexpr uint64_t kCachedPlanes = 264 * kMiB;
+inline bool planes_around_l2(const void* first, uint64_t n, uint64_t bytes, bool messages) {
+    const uint64_t total = n * bytes;
+    if (n % 32 || (uintptr_t)first % 128) return messages && total <= 16 * kMiB;
+    return total <= 56 * kMiB || (total > kCachedPlanes && n > (1u << 21));
+}
 
-// Read by XCD through the L2 where the 256 MB memory-side cache holds most of
-// them, else around it in block order, so that the part which a writer just
-// left there is not evicted before it is read.  Expansion and online call,
-// N = 19, us (cached by XCD / around the L2 in block order):
-//   1,000,003 54 / 56   4,000,003 255 / 213   8,000,003 475 / 428   2^20 54 / 61   2^23 463 / 389
-// P2's reply alone: 1,000,003 16.8 / 20.0, 1,500,001 24.1 / 29.9, 4,000,003 83 / 81.
-inline bool planes_cached(uint64_t n, uint64_t bytes) { return n * bytes <= (320ull << 20); }
+// Read by XCD through the L2 where they were written so and the 256 MB
+// memory-side cache holds most of them, else around it in block order, so that
+// the part which a writer just left there is not evicted before it is read.
+// The same sequences, cached by XCD / around the L2 after a writer through it:
+// N = 28, 2^20, 252 1 / 1.10; N = 19, 2^21, 264 equal; N = 10, 6,422,528, 269
+// 1.13 / 1; N = 32, 1,000,003, 274 1.16 / 1; N = 15, 4,000,003, 305 1.33 / 1.
+inline bool planes_cached(const void* first, uint64_t n, uint64_t bytes, bool messages) {
+    return !planes_around_l2(first, n, bytes, messages) && n * bytes <= kCachedPlanes;
+}
+
+// Records of at most this many bytes an element always go around the L2: their
+// kernels are bound by the VALU, and shared lines cost them little (N = 9, 36
+// bytes: 524,289 elements 1 / 1.11, 4,000,003 1.02 / 1; N = 10, 44 bytes:
+// 1,000,003 equal, 4,000,003 1.15 / 1).
+constexpr uint64_t kSmallRecord = 40;
 
 // Fully validated replicated-sharing DReLU/ReLU launch (Alg. drelu2).
 struct RssLaunch {

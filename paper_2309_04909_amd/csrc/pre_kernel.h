@@ -277,7 +277,9 @@ hipError_t launch_pre_field(const PreLaunch& L, const F& f, hipStream_t st) {
         A.s01 = Stream{L.s01.k0, L.s01.k1, L.s01.n0, L.s01.n1};
         A.s02 = Stream{L.s02.k0, L.s02.k1, L.s02.n0, L.s02.n1};
         A.s12 = Stream{L.s12.k0, L.s12.k1, L.s12.n0, L.s12.n1};
-        return launch_expand<T, N, F, RELU, planes_around_l2(bytes)>(L, A, f, st);
+        if constexpr (bytes > kSmallRecord)
+            if (!planes_around_l2(A.perm, L.n, bytes, false)) return launch_expand<T, N, F, RELU, false>(L, A, f, st);
+        return launch_expand<T, N, F, RELU, true>(L, A, f, st);
     }
     PreKArgs A;
     A.x0 = L.x0;
@@ -296,8 +298,8 @@ hipError_t launch_pre_field(const PreLaunch& L, const F& f, hipStream_t st) {
     A.s02 = Stream{L.s02.k0, L.s02.k1, L.s02.n0, L.s02.n1};
     A.s12 = Stream{L.s12.k0, L.s12.k1, L.s12.n0, L.s12.n1};
     if (L.cap) return launch_pre<T, N, F, RELU, true, true>(L, A, f, st);
-    if constexpr (!planes_around_l2(bytes))
-        if (planes_cached(L.n, bytes)) return launch_pre<T, N, F, RELU, false, false>(L, A, f, st);
+    if constexpr (bytes > kSmallRecord)
+        if (planes_cached(A.perm, L.n, bytes, false)) return launch_pre<T, N, F, RELU, false, false>(L, A, f, st);
     return launch_pre<T, N, F, RELU, false, true>(L, A, f, st);
 }
 

@@ -70,7 +70,7 @@ __device__ __forceinline__ uint64_t unpack_slot(const uint32_t (&w)[Packing<N>::
     return v & ((1ull << N) - 1);
 }
 
-template <typename T, int N, typename F, int PARTY>
+template <typename T, int N, typename F, int PARTY, bool NT>
 __global__ BC_KERNEL_ATTRS void k_send(SplitKArgs A, F f_arg) {
     using FT = typename F::T;
     constexpr int W = Packing<N>::W;
@@ -78,7 +78,7 @@ __global__ BC_KERNEL_ATTRS void k_send(SplitKArgs A, F f_arg) {
     const T* X = static_cast<const T*>(A.in0);
     uint32_t* M = static_cast<uint32_t*>(A.out0);
     const T mask = in_vgpr((T)A.ring_mask);
-    const WalkRange R = walk_range<true>((uint32_t)(A.end - A.begin));
+    const WalkRange R = walk_range<!NT>((uint32_t)(A.end - A.begin));
     for (uint64_t e = A.begin + R.begin; e < A.begin + R.end; e += R.stride) {
         const Index g = Index::of(A.elem_base + A.begin, e - A.begin);
         const T x = X[e] & mask;
@@ -99,7 +99,7 @@ __global__ BC_KERNEL_ATTRS void k_send(SplitKArgs A, F f_arg) {
             pack_slot<N>(words, j, (uint64_t)party_message<T, N, F, PARTY>(ak, sig.pos(j), sig.times(j), r, z, f));
         }
 #pragma unroll
-        for (int k = 0; k < W; ++k) M[(uint64_t)k * A.n + e] = words[k];   // through the L2, by XCD: see planes_around_l2
+        for (int k = 0; k < W; ++k) st_plane<NT>(&M[(uint64_t)k * A.n + e], words[k]);
     }
 }
 
@@ -167,15 +167,15 @@ inline SplitKArgs make_split_kargs(const SplitLaunch& L) {
     return A;
 }
 
-template <typename T, int N, typename F>
+template <typename T, int N, typename F, bool NT>
 hipError_t launch_send(const SplitLaunch& L, SplitKArgs A, const F& f, hipStream_t st) {
     return by_index_range(L.elem_base, L.n, [&](uint64_t begin, uint64_t end) {
         A.begin = begin;
         A.end = end;
         if (L.party == 0)
-            hipLaunchKernelGGL((k_send<T, N, F, 0>), dim3(walk_grid(true, L.grid)), dim3(256), 0, st, A, f);
+            hipLaunchKernelGGL((k_send<T, N, F, 0, NT>), dim3(walk_grid(!NT, L.grid)), dim3(256), 0, st, A, f);
         else
-            hipLaunchKernelGGL((k_send<T, N, F, 1>), dim3(walk_grid(true, L.grid)), dim3(256), 0, st, A, f);
+            hipLaunchKernelGGL((k_send<T, N, F, 1, NT>), dim3(walk_grid(!NT, L.grid)), dim3(256), 0, st, A, f);
     });
 }
 
@@ -190,13 +190,15 @@ hipError_t launch_reply(const SplitLaunch& L, SplitKArgs A, const F& f, hipStrea
 
 template <typename T, int N>
 hipError_t launch_split_exact(const SplitLaunch& L, hipStream_t st) {
-    constexpr uint64_t bytes = 4 * Packing<N>::W;          // of one message an element
+    constexpr uint64_t bytes = 8 * Packing<N>::W;          // of both messages an element
     const SplitKArgs A = make_split_kargs(L);
     return with_field<N>(L.p, [&](auto f) {
         using F = decltype(f);
-        if (L.kind == SplitLaunch::SEND) return launch_send<T, N, F>(L, A, f, st);
-        return planes_cached(L.n, 2 * bytes) ? launch_reply<T, N, F, false>(L, A, f, st)
-                                             : launch_reply<T, N, F, true>(L, A, f, st);
+        if (L.kind == SplitLaunch::SEND)
+            return planes_around_l2(A.out0, L.n, bytes, true) ? launch_send<T, N, F, true>(L, A, f, st)
+                                                              : launch_send<T, N, F, false>(L, A, f, st);
+        return planes_cached(A.in0, L.n, bytes, true) ? launch_reply<T, N, F, false>(L, A, f, st)
+                                                      : launch_reply<T, N, F, true>(L, A, f, st);
     });
 }
 

@@ -121,7 +121,7 @@ def tune_kind(kind, settings, n, reps, ops=(B.BC_OP_DRELU, B.BC_OP_RELU)):
             else:
                 fn = lambda: B.rand_expand(op, prm, sd, n, out=rand)  # noqa: E731
             ref, best = None, None
-            for bpc in BPC:
+            for bpc in BPC + ([256] if kind == "expand" else []):
                 B.set_schedule(kind, npos, bpc, width, op)
                 ms = _time(fn, reps)
                 if kind != "expand":

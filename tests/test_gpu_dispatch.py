@@ -26,3 +26,14 @@ def test_finish_grid(B, ell, lx, per_unit):
         for party in (0, 1):
             (name, blocks), = kernels(lambda: B.drelu_finish(party, d, prm, sd, out=d))
             assert "k_finish" in name and blocks == min((n + 255) // 256, units * per_unit), n
+
+
+@pytest.mark.parametrize("op", [0, 1])
+def test_expansion_without_a_stride(B, op):
+    """The N = 19 expansion, bound by its writes, takes 2^24 elements in one order (a grid that strides
+    writes two regions of every plane at once)."""
+    from graph_kernels import kernels
+    prm, sd, n = B.Params(64, 18, 13), B.Seeds(1, 2, 3, 4), 1 << 24
+    rec = torch.empty(B.rand_bytes(op, prm, n), dtype=torch.uint8, device="cuda")
+    (name, blocks), = kernels(lambda: B.rand_expand(op, prm, sd, n, out=rec))
+    assert "k_expand" in name and blocks * 256 == n

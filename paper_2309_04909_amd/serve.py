@@ -71,6 +71,16 @@ class Launch:
     bytes: int = 0
 
 
+def sizes_by_lanes(units: int, most: int, fill: int):
+    """Call sizes that take every number of lanes per element the library uses
+    (4, 2 or 1; `most` and `fill` are the schedule's values of the kinds
+    "group" and "group_fill", `units` the compute units): several lanes while
+    the call's waves stay within `fill` on each of a unit's four SIMDs."""
+    threads = units * 4 * 64 * fill
+    limits = [threads // lanes for lanes in (4, 2) if most >= lanes]
+    return limits + [limits[-1] + 1 if limits else 100]
+
+
 class Server:
     def __init__(self, pools, params, seeds: B.Seeds, hbm_budget: int, max_slots: int = 256, nstreams: int = 4,
                  keep_outputs: bool = False, rand_budget: int = 0, on_done=None, max_batch: int = 0):
@@ -112,10 +122,12 @@ class Server:
         while len(self._pinned) < 2 * len(self.streams):        # a plan per ring and stream
             self._pinned.append((torch.empty(need, dtype=torch.uint8, pin_memory=True),
                                  torch.empty(need, dtype=torch.uint8, device=dev)))
+        units = torch.cuda.get_device_properties(dev).multi_processor_count
         for ell, (x0, x1) in self.pools.items():
             prm = self.params[ell]
-            for fn in (B.drelu, B.relu):
-                for n in (100, 12000, 70000):
+            for fn, op in ((B.drelu, B.BC_OP_DRELU), (B.relu, B.BC_OP_RELU)):
+                most, fill = (B.get_schedule(kind, prm.npos, x0.element_size(), op) for kind in ("group", "group_fill"))
+                for n in sizes_by_lanes(units, most, fill):
                     m = min(n, x0.numel())
                     fn(x0[:m], x1[:m], prm, self.seeds)
             m = min(1000, x0.numel())

@@ -201,7 +201,9 @@ int bc_zp_mul_add(const uint64_t* a, const uint64_t* b, const uint64_t* d, uint6
                                  the largest number of lanes per element
                                  (1 = off, 2, 4 or more for up to 4; default
                                  8); the replicated-sharing calls take 4
-                                 where it gives more than 1               */
+                                 where it gives more than 1 (at l_x = 32
+                                 where it gives 4), and 1 with a prime
+                                 other than the default               */
 #define BC_SCHED_GROUP_FILL 6u /* the same calls: several lanes per element
                                  are used while n times the lanes stays
                                  within this many waves per SIMD (default 2) */

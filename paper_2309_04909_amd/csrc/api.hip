@@ -343,7 +343,8 @@ int rss_common(bool relu, const void* x0, const void* x1, const void* x2, void* 
     L.s012 = stream_key(seeds->seed012, seeds->nonce);
     L.s2 = stream_key(seeds->seed2, seeds->nonce);
     const int lanes = lanes_per_element(L.npos, w, relu, n, capture != nullptr);
-    L.waves = lanes == 4 || (lanes == 2 && L.npos <= 32);
+    // k_rss_waves is built for the default primes only
+    L.waves = r.p == default_prime(r.lx) && (lanes == 4 || (lanes == 2 && L.npos <= 32));
     L.grid = (int)sched_grid(BC_SCHED_FUSED, L.npos, w, relu, (n * (L.waves ? 4u : 1u) + 255) / 256);
     hipStream_t st = (hipStream_t)stream;
     hipError_t e;

@@ -37,3 +37,26 @@ def test_expansion_without_a_stride(B, op):
     rec = torch.empty(B.rand_bytes(op, prm, n), dtype=torch.uint8, device="cuda")
     (name, blocks), = kernels(lambda: B.rand_expand(op, prm, sd, n, out=rec))
     assert "k_expand" in name and blocks * 256 == n
+
+
+@pytest.mark.parametrize("lx", [18, 32])
+@pytest.mark.parametrize("n", [1, 1000, 32768, 32769, 65536, 65537])
+def test_replicated_sharing_kernel_and_grid(B, n, lx):
+    """Small replicated-sharing calls split their slots over four waves, with the default prime only; the grid
+    is the one of the kernel that runs."""
+    import sympy
+    from graph_kernels import kernels, lanes
+    fill = 2 * 256 * torch.cuda.get_device_properties(0).multi_processor_count
+    before = {(k, op): B.get_schedule(k, lx + 1, 8, op) for k in ("group", "group_fill") for op in (0, 1)}
+    x = tuple(torch.zeros(n, dtype=torch.int64, device="cuda") for _ in range(3))
+    try:
+        B.set_schedule("group", lx + 1, 4, 8)
+        B.set_schedule("group_fill", lx + 1, 2, 8)
+        for p in (0, int(sympy.prevprime(B.default_prime(lx)))):
+            prm = B.Params(64, lx, 0, p)
+            (name, blocks), = kernels(lambda: B.rss_relu(x, prm, B.RssSeeds(1, 2, 3, 4, 5), out=x))
+            want = 4 if p == 0 and (4 * n <= fill or (lx < 32 and 2 * n <= fill)) else 1
+            assert lanes(name) == want and blocks == (n * want + 255) // 256, (p, name, blocks)
+    finally:
+        for (k, op), v in before.items():
+            B.set_schedule(k, lx + 1, v, 8, op)

@@ -7,14 +7,15 @@ uint64/int64 storage), contiguous.  Calls enqueue on the current torch
 stream unless a stream is given.  The calls on share
 arrays (drelu, relu, their truncating and replicated forms, trunc_det,
 mul_trunc and the parties-apart calls) are marshalled by the native module
-_fastcall where their arguments are plain, and through ctypes by the code
-here otherwise: the same checks and the same C call.  If the library or the
-module is not built, importing this module raises ImportError: there is no
-fallback path.
+_fastcall where it loads and their arguments are plain, and through ctypes by
+the code here otherwise: the same checks and the same C call.  If the library
+is not built, importing this module raises ImportError: there is no fallback
+path.
 """
 
 import ctypes
 import os
+import warnings
 from dataclasses import dataclass
 
 import torch
@@ -140,11 +141,18 @@ def _load():
 
 lib = _load()
 
+
+class _CtypesOnly:
+    """In the place of _fastcall: leaves every call to the ctypes path."""
+    drelu = trunc = cut = rss = mul = send = reply = finish = set_check = staticmethod(lambda *args: None)
+
+
 try:
     from . import _fastcall
-except ImportError as e:
-    raise ImportError(f"the _fastcall module beside {LIB_PATH} is not built; run __graft_entry__.build() "
-                      "or python -m paper_2309_04909_amd.build") from e
+except ImportError as e:                             # not built, or built for another torch or Python
+    warnings.warn(f"the _fastcall module beside {LIB_PATH} does not load ({e}); calls are marshalled through ctypes, "
+                  "about 2 us slower each; run __graft_entry__.build()", RuntimeWarning)
+    _fastcall = _CtypesOnly
 
 
 def _address(fn):

@@ -73,6 +73,14 @@ const at::Tensor* plain_tensor(PyObject* o, uint32_t width) {
     return &t;
 }
 
+// The interpreter lock released for a scope, also when the scope is left by
+// an exception: the C calls, as ctypes makes them, and the allocations, which
+// can wait for the device.
+struct Unlocked {
+    PyThreadState* state = PyEval_SaveThread();
+    ~Unlocked() { PyEval_RestoreThread(state); }
+};
+
 // An owned reference to a call's result.
 struct Result {
     PyObject* o = nullptr;
@@ -100,7 +108,11 @@ bool take_stream(PyObject* stream, const at::Tensor& t, void** out) {
 bool take_output(PyObject* given, const at::Tensor& like, at::IntArrayRef sizes, at::ScalarType dtype, uint32_t width,
                  int64_t n, PyObject** o, void** ptr) {
     if (given == Py_None) {
-        at::Tensor t = at::empty(sizes, like.options().dtype(dtype).requires_grad(false));
+        at::Tensor t;
+        {
+            Unlocked unlocked;
+            t = at::empty(sizes, like.options().dtype(dtype).requires_grad(false));
+        }
         *ptr = t.data_ptr();
         *o = THPVariable_Wrap(std::move(t));
         if (!*o) PyErr_Clear();
@@ -170,11 +182,8 @@ PyObject* conclude(Result& result, int rc, PyObject* name) {
 // fn(args) without the GIL, as ctypes calls it.
 template <typename Fn>
 int unlocked(Fn&& fn) {
-    int rc;
-    Py_BEGIN_ALLOW_THREADS
-    rc = fn();
-    Py_END_ALLOW_THREADS
-    return rc;
+    Unlocked u;
+    return fn();
 }
 
 using DreluFn = int (*)(const void*, const void*, void*, void*, uint64_t, const bc_drelu_params*, const bc_seeds*, uint64_t,

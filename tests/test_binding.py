@@ -94,3 +94,93 @@ def test_other_threads_run_while_outputs_are_allocated(tmp_path):
     del got
     del pool
     del allocator
+
+
+def native_calls(B, prm, x, n):
+    """Every native function: (name, a call of it with plain arguments, the same call of the binding)."""
+    sd, rs, dt = B.Seeds(7, 8, 9, 10), B.RssSeeds(1, 2, 3, 4, 5, 6), x[0].dtype
+    low = prm.ell - 3
+    lower = B.Params(low, prm.lx, 0)
+    m = [B.drelu_send(p, x[p], prm, sd) for p in (0, 1)]
+    d = B.drelu_reply(*m, prm, sd)[0].view(dt)
+    F = B._fastcall
+    return [
+        ("drelu", lambda out, a: F.drelu(B._A_DRELU, "drelu", a[0], a[1], prm, sd, 5, out, None), 2,
+         lambda **k: B.drelu(x[0], x[1], prm, sd, elem_base=5, **k)),
+        ("relu", lambda out, a: F.drelu(B._A_RELU, "relu", a[0], a[1], prm, sd, 5, out, None), 2,
+         lambda **k: B.relu(x[0], x[1], prm, sd, elem_base=5, **k)),
+        ("trunc_drelu", lambda out, a: F.trunc(B._A_TRUNC_DRELU, "trunc_drelu", a[0], a[1], prm.ell, 3, lower, sd, 5, out, None), 2,
+         lambda **k: B.trunc_drelu(x[0], x[1], prm.ell, 3, lower, sd, elem_base=5, **k)),
+        ("trunc_relu", lambda out, a: F.trunc(B._A_TRUNC_RELU, "trunc_relu", a[0], a[1], prm.ell, 3, lower, sd, 5, out, None), 2,
+         lambda **k: B.trunc_relu(x[0], x[1], prm.ell, 3, lower, sd, elem_base=5, **k)),
+        ("trunc_det", lambda out, a: F.cut(B._A_TRUNC_DET, "trunc_det", a[0], a[1], prm.ell, 3, 2, out, None), 2,
+         lambda **k: B.trunc_det(x[0], x[1], prm.ell, 3, 2, **k)),
+        ("rss_drelu", lambda out, a: F.rss(B._A_RSS_DRELU, "rss_drelu", tuple(a[:3]), prm, rs, 5, out, None), 3,
+         lambda **k: B.rss_drelu(tuple(x[:3]), prm, rs, elem_base=5, **k)),
+        ("rss_relu", lambda out, a: F.rss(B._A_RSS_RELU, "rss_relu", tuple(a[:3]), prm, rs, 5, out, None), 3,
+         lambda **k: B.rss_relu(tuple(x[:3]), prm, rs, elem_base=5, **k)),
+        ("mul_trunc", lambda out, a: F.mul(B._A_MUL, "mul_trunc", *a, prm.ell, 4, B.BC_TRUNC_BEFORE, sd, 5, out, None), 2,
+         lambda **k: B.mul_trunc(*x, prm.ell, 4, B.BC_TRUNC_BEFORE, sd, elem_base=5, **k)),
+        ("drelu_send", lambda out, a: F.send(B._A_SEND, "drelu_send", 1, a[0], prm, sd, 5, out, None), 0,
+         lambda **k: B.drelu_send(1, x[0], prm, sd, elem_base=5, **k)),
+        ("drelu_reply", lambda out, a: F.reply(B._A_REPLY, "drelu_reply", *([m[0], m[1]] if a is x else [a[0], m[1]]), prm, sd, 5, out, None), 2,
+         lambda **k: B.drelu_reply(m[0], m[1], prm, sd, elem_base=5, **k)),
+        ("drelu_finish", lambda out, a: F.finish(B._A_FINISH, "drelu_finish", 1, d if a is x else a[0], prm, sd, 5, out, None), 1,
+         lambda **k: B.drelu_finish(1, d, prm, sd, elem_base=5, **k)),
+    ]
+
+
+class Subclass(torch.Tensor):
+    """A tensor type that the native path does not take."""
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [1, 5001])
+@pytest.mark.parametrize("ell,lx,k_lo", [(64, 18, 13), (51, 11, 13), (32, 8, 8)])
+def test_the_native_path_is_taken_and_agrees_with_ctypes(monkeypatch, ell, lx, k_lo, n):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2309_04909_amd import bicop as B
+    prm = B.Params(ell, lx, k_lo)
+    dt = torch.int64 if ell > 32 else torch.int32
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    x = [torch.randint(-(1 << 62), 1 << 62, (n,), generator=gen, device="cuda").bitwise_and_((1 << ell) - 1 if ell < 64 else -1).to(dt)
+         for _ in range(4)]
+    odd = [t.as_subclass(Subclass) for t in x]
+    results = {}
+    for name, native, outputs, call in native_calls(B, prm, x, n):
+        def flat(r):
+            return [t.view(torch.int32) for t in (r if isinstance(r, tuple) else (r,))]
+        got = native(None, x)
+        assert got is not None, f"{name}: plain arguments did not take the native path"
+        results[name] = flat(got)
+        if outputs > 1:
+            like = [torch.empty_like(t) for t in (got if isinstance(got, tuple) else (got,))]
+            assert native(tuple(like), x) is not None and native(like, x) is None, f"{name}: outputs"
+        assert native(None, odd) is None, f"{name}: a subclass took the native path"
+        side = torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(side):                        # stream=None: the current one
+            again = flat(native(None, x))
+        side.synchronize()
+        for a, b in zip(again, results[name]):
+            assert torch.equal(a, b), name
+    monkeypatch.setattr(B, "_fastcall", B._CtypesOnly)
+    for name, _, _, call in native_calls(B, prm, x, n):
+        for a, b in zip(flat(call()), results[name]):
+            assert torch.equal(a, b), name
+
+
+@pytest.mark.gpu
+def test_the_native_path_enqueues_on_the_current_stream():
+    """Captured on a stream made current, the call is a node of the graph; on any other it could not be captured."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from graph_kernels import kernels
+    from paper_2309_04909_amd import bicop as B
+    x, out = torch.zeros(1000, dtype=torch.int64, device="cuda"), torch.empty(1000, dtype=torch.int64, device="cuda")
+    prm, sd = B.Params(64, 7, 11), B.Seeds(1, 2, 3)
+
+    def call():
+        assert B._fastcall.drelu(B._A_DRELU, "drelu", x, x, prm, sd, 0, (out, out), None) is not None
+    assert len(kernels(call)) == 1

@@ -212,10 +212,18 @@ std::atomic<uint32_t> g_sched[kKinds][34][2][2];
 // 365 / 338 us; 2^24 84.8 / 82.6 / 82.3.
 constexpr uint32_t kDefaultBpc[kKinds] = {64, 1024, 64, 64, 64, 8, 2};
 
+// The DReLU with two windows (l_x = 1) is bound by memory, and its threads gain
+// from the next element's shares in flight before the compute units fill up: us
+// at 16 / 64 blocks a unit, l = 64: 2,000,003 elements 13.5 / 15.5, 4,000,003
+// 24.6 / 29.0, 8,000,003 48 / 46, 2^24 102 / 92 (three windows: 4,000,003
+// 25.9 / 30.6, 2^24 105 / 102).
+constexpr uint32_t kTwoWindowsBpc = 16;
+
 uint32_t sched_value(uint32_t kind, uint32_t npos, uint32_t width, bool relu) {
     const uint32_t v =
         g_sched[kind][npos < 34 ? npos : 0][width == 4 ? 0 : 1][relu ? 1 : 0].load(std::memory_order_relaxed);
-    return v ? v : kDefaultBpc[kind];
+    if (v) return v;
+    return kind == BC_SCHED_FUSED && npos == 2 && !relu ? kTwoWindowsBpc : kDefaultBpc[kind];
 }
 
 // Lanes per element of a DReLU/ReLU call (one lane in each of G waves, which

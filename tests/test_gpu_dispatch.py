@@ -60,3 +60,14 @@ def test_replicated_sharing_kernel_and_grid(B, n, lx):
     finally:
         for (k, op), v in before.items():
             B.set_schedule(k, lx + 1, v, 8, op)
+
+
+def test_two_window_drelu_grid(B):
+    """The DReLU at l_x = 1 strides above 16 blocks a compute unit, wider ones above 64."""
+    from graph_kernels import kernels
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    n = 256 * 64 * units + 1
+    x, y = (torch.zeros(n, dtype=torch.int64, device="cuda") for _ in range(2))
+    for lx, per_unit in ((1, 16), (2, 64)):
+        (_, blocks), = kernels(lambda: B.drelu(x, x, B.Params(64, lx, 13), B.Seeds(1, 2, 3), out=(y, y)))
+        assert blocks == per_unit * units

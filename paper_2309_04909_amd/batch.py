@@ -46,21 +46,21 @@ def _records(params: B.Params, segments):
     return recs
 
 
-# Blocks that an MI355X holds at once: 256 compute units, 8 blocks of 256
-# threads on a unit.
-RESIDENT_BLOCKS = 2048
+# Blocks that one compute unit holds at once: 8 of 256 threads.
+RESIDENT_BLOCKS = 8
 
 
-def default_tile(elements: int) -> int:
-    """Elements per tile of a batch that names none: the autotuned size where
-    it gives every resident block a tile, else halved until it does, down to
-    256 (one element a thread).  A large tile spares its prologue and keeps
-    the next element's shares in flight, which decides only once the chip is
-    full.  Measured, us at tiles of 256 / 512 / 1,024 (ReLU, l_x = 7):
-    230,801 elements 7.7 / 8.4 / 11.7; 577,003 12.9 / 13.6 / 16.4; 1,154,006
-    21.9 / 21.0 / 22.8; 2,308,012 39.3 / 36.8 / 37.0; 4,616,024 72 / 66 / 62.6."""
+def default_tile(elements: int, units: int = 256) -> int:
+    """Elements per tile of a batch that names none, on a device of `units`
+    compute units: the autotuned size where it gives every resident block a
+    tile, else halved until it does, down to 256 (one element a thread).  A
+    large tile spares its prologue and keeps the next element's shares in
+    flight, which decides only once the chip is full.  Measured on 256 units,
+    us at tiles of 256 / 512 / 1,024 (ReLU, l_x = 7): 230,801 elements 7.7 /
+    8.4 / 11.7; 577,003 12.9 / 13.6 / 16.4; 1,154,006 21.9 / 21.0 / 22.8;
+    2,308,012 39.3 / 36.8 / 37.0; 4,616,024 72 / 66 / 62.6."""
     tile = int(B.SCHEDULES.get("batch_tile", 0)) or 1024
-    while tile > 256 and elements < RESIDENT_BLOCKS * tile:
+    while tile > 256 and elements < RESIDENT_BLOCKS * units * tile:
         tile //= 2
     return tile
 
@@ -95,7 +95,7 @@ class RaggedBatch:
         self.params = params
         self.seeds = seeds
         if tile_elems == 0:
-            tile_elems = default_tile(elements)
+            tile_elems = default_tile(elements, torch.cuda.get_device_properties(device).multi_processor_count)
         self.grid = grid
         self.device = device
         nbytes = self.plan_bytes(nseg)

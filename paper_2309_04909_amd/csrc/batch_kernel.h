@@ -17,6 +17,8 @@ struct BatchKArgs {
 // 32-bit offsets from the tile's start): each thread walks its elements with
 // the next one's shares loaded before the current one is computed (raw
 // buffer loads over the tile, which read 0 past its end), as k_drelu does.
+// Unlike there the pointers come from a segment record in memory, so the
+// stores are FLAT accesses, and each element waits for the last one's.
 template <typename T, int N, typename F, bool RELU>
 __device__ __forceinline__ void tile_elements(const T* X0, const T* X1, T* Y0, T* Y1, uint64_t e0, uint64_t e1,
                                               uint64_t base, T mask, T in_mask, uint32_t k_in, uint32_t k_lo,

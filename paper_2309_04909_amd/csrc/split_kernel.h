@@ -79,6 +79,8 @@ __global__ BC_KERNEL_ATTRS void k_send(SplitKArgs A, F f_arg) {
     uint32_t* M = static_cast<uint32_t*>(A.out0);
     const T mask = in_vgpr((T)A.ring_mask);
     const WalkRange R = walk_range<!NT>((uint32_t)(A.end - A.begin));
+    // a 64-bit element: with a 32-bit offset from scalar bases the compiler
+    // keeps a pointer for every word plane (N = 32: 98 registers for 79)
     for (uint64_t e = A.begin + R.begin; e < A.begin + R.end; e += R.stride) {
         const Index g = Index::of(A.elem_base + A.begin, e - A.begin);
         const T x = X[e] & mask;

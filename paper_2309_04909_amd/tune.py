@@ -3,7 +3,7 @@
 For each kernel kind and setting of the workloads it times a sweep of grid
 sizes (blocks of 256 threads per compute unit, so elements per thread
 = n / (grid * 256)), for the DReLU and the ReLU kernels apart; for small
-calls it sweeps the lanes per element (1, 4 or 8 lanes share an element);
+calls it sweeps the lanes per element (1, 2 or 4 lanes share an element);
 for the ragged batch it also sweeps the tile size.  Entries are keyed by
 (kind, window count, storage width, op), the key of the library's table, so
 two settings that share a window count keep their own schedules.  Results

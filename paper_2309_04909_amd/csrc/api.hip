@@ -5,6 +5,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <atomic>
 #include <mutex>
 
@@ -212,18 +213,29 @@ std::atomic<uint32_t> g_sched[kKinds][34][2][2];
 // 365 / 338 us; 2^24 84.8 / 82.6 / 82.3.
 constexpr uint32_t kDefaultBpc[kKinds] = {64, 1024, 64, 64, 64, 8, 2};
 
-// The DReLU with two windows (l_x = 1) is bound by memory, and its threads gain
-// from the next element's shares in flight before the compute units fill up: us
-// at 16 / 64 blocks a unit, l = 64: 2,000,003 elements 13.5 / 15.5, 4,000,003
-// 24.6 / 29.0, 8,000,003 48 / 46, 2^24 102 / 92 (three windows: 4,000,003
-// 25.9 / 30.6, 2^24 105 / 102).
-constexpr uint32_t kTwoWindowsBpc = 16;
+// The table's entry, 0 where nothing set it.
+uint32_t sched_entry(uint32_t kind, uint32_t npos, uint32_t width, bool relu) {
+    return g_sched[kind][npos < 34 ? npos : 0][width == 4 ? 0 : 1][relu ? 1 : 0].load(std::memory_order_relaxed);
+}
 
 uint32_t sched_value(uint32_t kind, uint32_t npos, uint32_t width, bool relu) {
-    const uint32_t v =
-        g_sched[kind][npos < 34 ? npos : 0][width == 4 ? 0 : 1][relu ? 1 : 0].load(std::memory_order_relaxed);
-    if (v) return v;
-    return kind == BC_SCHED_FUSED && npos == 2 && !relu ? kTwoWindowsBpc : kDefaultBpc[kind];
+    const uint32_t v = sched_entry(kind, npos, width, relu);
+    return v ? v : kDefaultBpc[kind];
+}
+
+// The most blocks of a DReLU with two windows (l_x = 1) and one block's work in
+// each of `work` blocks, where nothing tuned it.  It is bound by memory, and its
+// threads gain from the next element's shares in flight before the compute
+// units fill up: two to four elements a thread, until the default grid gives
+// them as many.  Us at 16 / 32 / 64 blocks a unit, l = 64: 2,000,003 elements
+// 12.9 / 14.0 / 13.5, 4,000,003 24.7 / 23.6 / 27.2, 6,000,001 38.1 / 34.5 / 35.8,
+// 8,000,003 46.7 / 48.0 / 50.0, 10,000,003 60.1 / 57.0 / 55.6, 2^24 97.5 / 95.0 /
+// 91.0; l = 32: 4,000,003 18.0 / 18.6 / 22.0, 8,000,003 33.7 / 33.1 / 35.5, 2^24 73 /
+// 69 / 67.  The replicated form and the parties' own kernels differ by less and
+// keep the default (replicated: 4,000,003 48.7 / 45.9 / 47.5, 2^24 205 / 197 / 193).
+uint64_t two_window_blocks(uint64_t work) {
+    const uint64_t full = (uint64_t)grid_cap((int)kDefaultBpc[BC_SCHED_FUSED]);
+    return work <= full ? full / 4 : work <= 2 * full ? full / 2 : full;
 }
 
 // Lanes per element of a DReLU/ReLU call (one lane in each of G waves, which
@@ -295,7 +307,10 @@ int drelu_common(uint32_t op, const void* x0, const void* x1, void* y0, void* y1
     L.s12 = stream_key(seeds->seed12, seeds->nonce);
     L.block = 256;
     L.group = lanes_per_element(L.npos, w, op == BC_OP_RELU, n, capture != nullptr);
-    L.grid = (int)sched_grid(BC_SCHED_FUSED, L.npos, w, op == BC_OP_RELU, (n * (uint64_t)L.group + 255) / 256);
+    uint64_t work = (n * (uint64_t)L.group + 255) / 256;
+    if (L.npos == 2 && op == BC_OP_DRELU && !sched_entry(BC_SCHED_FUSED, L.npos, w, false))
+        work = std::min(work, two_window_blocks(work));
+    L.grid = (int)sched_grid(BC_SCHED_FUSED, L.npos, w, op == BC_OP_RELU, work);
     hipStream_t st = (hipStream_t)stream;
     hipError_t e;
     const bool relu = op == BC_OP_RELU;

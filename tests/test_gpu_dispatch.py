@@ -63,11 +63,28 @@ def test_replicated_sharing_kernel_and_grid(B, n, lx):
 
 
 def test_two_window_drelu_grid(B):
-    """The DReLU at l_x = 1 strides above 16 blocks a compute unit, wider ones above 64."""
+    """The DReLU at l_x = 1 takes a quarter, then half of the default 64 blocks a compute unit while those give a
+    thread one and two elements; larger calls, wider windows and the other kernels of the window count take it all."""
     from graph_kernels import kernels
     units = torch.cuda.get_device_properties(0).multi_processor_count
-    n = 256 * 64 * units + 1
-    x, y = (torch.zeros(n, dtype=torch.int64, device="cuda") for _ in range(2))
-    for lx, per_unit in ((1, 16), (2, 64)):
-        (_, blocks), = kernels(lambda: B.drelu(x, x, B.Params(64, lx, 13), B.Seeds(1, 2, 3), out=(y, y)))
-        assert blocks == per_unit * units
+    full = 64 * units
+    x, y = (torch.zeros(512 * full + 1, dtype=torch.int64, device="cuda") for _ in range(2))
+    sd, prm = B.Seeds(1, 2, 3), B.Params(64, 1, 13)
+    drelu = lambda n, p=prm: kernels(lambda: B.drelu(x[:n], x[:n], p, sd, out=(y[:n], y[:n])))  # noqa: E731
+    for n, want in ((256 * full, full // 4), (256 * full + 1, full // 2), (512 * full, full // 2), (512 * full + 1, full)):
+        (_, blocks), = drelu(n)
+        assert blocks == want, n
+    n = 256 * full + 1
+    (_, blocks), = drelu(n, B.Params(64, 2, 13))
+    assert blocks == full
+    message = torch.empty((B.msg_words(2), n), dtype=torch.int32, device="cuda")
+    (name, blocks), = kernels(lambda: B.drelu_send(0, x[:n], prm, sd, out=message))
+    assert "k_send" in name and blocks == full
+    (name, blocks), = kernels(lambda: B.rss_drelu((x[:n],) * 3, prm, B.RssSeeds(1, 2, 3, 4, 5), out=(y[:n],) * 3))
+    assert "k_rss" in name and blocks == full
+    try:
+        B.set_schedule("fused", 2, 3, 8, 0)
+        (_, blocks), = drelu(n)
+        assert blocks == 3 * units
+    finally:
+        B.set_schedule("fused", 2, 0, 8, 0)

@@ -140,7 +140,7 @@ constexpr uint64_t kCachedPlanes = 264 * kMiB;
 inline bool planes_around_l2(const void* first, uint64_t n, uint64_t bytes, bool messages) {
     const uint64_t total = n * bytes;
     if (n % 32 || (uintptr_t)first % 128) return messages && total <= 16 * kMiB;
-    return total <= 56 * kMiB || (total > kCachedPlanes && n > (1u << 21));
+    return n < (1u << 21) ? total <= 56 * kMiB : total > kCachedPlanes && n > (1u << 21);
 }
 
 // Read by XCD through the L2 where they were written so and the 256 MB

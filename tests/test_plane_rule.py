@@ -34,6 +34,8 @@ def test_rule(tmp_path):
         (256, 1 << 20, 56): (1, 0), (256, (1 << 20) + 32, 56): (0, 1),                             # 56 MiB and above
         (256, 1 << 20, 124): (0, 1), (256, 1 << 20, 264): (0, 1), (256, (1 << 20) + 32, 264): (0, 0),
         (256, 1 << 21, 288): (0, 0), (256, (1 << 21) + 32, 288): (1, 0), (256, (1 << 21) + 32, 100): (0, 1),
+        (256, (1 << 21) - 32, 8): (1, 0), (256, 1 << 21, 8): (0, 1), (256, 1 << 21, 16): (0, 1),   # few bytes each
+        (256, (1 << 21) - 32, 16): (1, 0), (256, 1 << 22, 8): (0, 1), (256, 1 << 26, 8): (1, 0),
         (256, 1 << 22, 80): (1, 0), (256, 1 << 23, 132): (1, 0),                                   # above the cache
     }
     shared = {                                                            # of a record, of messages
@@ -56,7 +58,11 @@ def test_rule(tmp_path):
 
 def sides(bytes_an_element):
     """Element counts around every limit, of whole and of shared lines."""
-    out = [1 << 21, (1 << 21) + 32] if bytes_an_element > 100 else []
+    out = []
+    if bytes_an_element > 100:
+        out = [1 << 21, (1 << 21) + 32]
+    elif bytes_an_element < 28:
+        out = [(1 << 21) - 32, 1 << 21]
     for limit, step in ((16 * MIB, 1), (56 * MIB, 32), (264 * MIB, 32), (264 * MIB, 1)):
         n = limit // bytes_an_element
         if step == 32:
@@ -69,7 +75,7 @@ def sides(bytes_an_element):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("setting,record,message", [((64, 18, 13), 124, 96), ((64, 9, 13), 44, 32)])
+@pytest.mark.parametrize("setting,record,message", [((64, 18, 13), 124, 96), ((64, 9, 13), 44, 32), ((64, 3, 13), 12, 8)])
 def test_both_sides_match_the_fused_call(setting, record, message):
     torch = pytest.importorskip("torch")
     if not torch.cuda.is_available():

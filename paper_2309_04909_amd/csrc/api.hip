@@ -207,7 +207,9 @@ std::atomic<uint32_t> g_sched[kKinds][34][2][2];
 // 9,232,384 elements at 8 / 16 / 64: l_x = 18 209 / 198 / 197 us, l_x = 11
 // (l = 51) 167 / 158 / 155, l_x = 8 (l = 32) 134 / 124 / 121; ReLU, its record's
 // expansion and its online call at l_x = 15, 4,000,003 elements, 16 / 64: 77 / 78,
-// 125 / 110, 92 / 82 (l_x = 23: 104 / 101, 320 / 292, 207 / 193).  Streaming calls
+// 125 / 110, 92 / 82 (l_x = 23: 104 / 101, 320 / 292, 207 / 193).  The committed
+// table has 256 for the expansion at l_x = 18, whose planes are then written in
+// one order (ReLU, 2^24 elements, 64 / 256: 411 / 355 us).  Streaming calls
 // are bound by memory, which is fastest when all blocks walk it in one order
 // without a stride: truncation at l = 64, 2^26 elements, 64 / 256 / 1024: 409 /
 // 365 / 338 us; 2^24 84.8 / 82.6 / 82.3.

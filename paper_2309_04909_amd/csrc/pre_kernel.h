@@ -73,10 +73,13 @@ __device__ __forceinline__ void pack_field(uint32_t (&w)[2], int off, uint32_t v
 }
 
 // Offline: expand the seeds of n elements into the record.  Bound by VALU
-// issue up to N = 9 (N = 8 ReLU: 364 instructions, 264 of them Philox; 388
+// issue up to N = 9 (N = 8 ReLU: 360 instructions, 264 of them Philox, 388
 // with 64-bit element addresses and the fields cut out of their products:
-// 3,211,264 elements 39.7 -> 37.8 us) and by the writes of the planes from
-// N = 16 on (5.3-5.8 TB/s through the L2, see planes_around_l2).
+// 3,211,264 elements 39.7 -> 37.8 us on one card, 34.3 on a faster one) and by
+// the writes of the planes from N = 16 on (planes_around_l2 has the two ways of
+// writing them).  The planes are global pointers: with generic ones and the
+// FLAT stores that they lead to, the N = 19 DReLU ran 514 instructions instead
+// of 496.
 template <typename T, int N, typename F, bool RELU, bool NT>
 __global__ BC_KERNEL_ATTRS void k_expand(ExpandKArgs A, F f) {
     const T mask = (T)A.ring_mask;
@@ -142,8 +145,10 @@ __device__ __forceinline__ RecordView<T> record_view(const void* rand, uint32_t 
 }
 
 // Online: bound by the reads of the record and the shares (N = 8 ReLU, 64 bytes
-// an element: 3,211,264 elements 37 us, 5.5 TB/s; N = 19: 5.0 TB/s).  Element
-// addresses are 32-bit offsets from scalar pointers (305 -> 302 instructions).
+// an element: 3,211,264 elements 36 us, 5.7 TB/s; N = 19, 2^24 elements: 458 us,
+// 5.7 TB/s).  Element addresses are 32-bit offsets from scalar pointers, of
+// every plane (against FLAT loads: N = 8 ReLU 302 -> 298 instructions, N = 19
+// DReLU 483 -> 465).
 // The input-dependent part of Alg. 7 (and of Alg. 8) for element i of
 // a range (every pointer, and the record's, at the range's start), reading its
 // draws from the record.  Reads X0[i], X1[i] (with k_in > 0,

@@ -12,7 +12,7 @@
 //               slot is 0], and writes its reply shares (rho, D' - rho).
 //   k_finish<P> P0 or P1 unflips its reply share with t.
 // Every step before P2 uses one share only, so k_send reads one array.  Sends
-// are bound by VALU issue up to N = 19 (591 instructions, 264 of them Philox,
+// are bound by VALU issue up to N = 19 (591 instructions, P1 609, 264 of them Philox,
 // 1,000,003 elements: 21 us) and by the message's writes above; the reply (202
 // instructions) and the finish by memory: N = 19, 16.6 us, 6.7 TB/s out of the
 // memory-side cache (21.6 us with nontemporal loads in block order).
